@@ -586,6 +586,15 @@ struct LdsStream {
   }
 };
 
+// Piece p (16 bytes) of row r of an unpadded row-major LDS tile of at least 16
+// pieces per row is kept at p ^ kswz(r), which keeps row-fragment and
+// transposing reads free of bank conflicts.
+__device__ __forceinline__ int kswz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
+
+template <int X>
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(X) : "memory");
+}
 __device__ __forceinline__ void wait_vm_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Workgroup barrier that orders LDS only: waits for this wave's LDS

@@ -34,8 +34,19 @@ namespace ccq {
 // sequential state pass needs no exponentials.
 // Blocks of 16: the diagonal blocks are inverted by forward substitution,
 // then wave w forms column block w, X_iw = -D_i sum_{m=w}^{i-1} A_im X_mw.
-template <typename T, int DK>
-__global__ __launch_bounds__(kThreads) void gdn_tri_kernel(const TriArgs a) {
+//
+// kWY also forms the operands of the WY state pass (gdn_wy_state_kernel), both
+// lane-native (16 bytes per lane, 1 KB per block, in the order a 16-row MFMA
+// operand is read): Tb = Tm diag(beta), the six blocks (I, kq) that are not
+// zero, and W = -Tm diag(beta e^gamma) K, blocks (I, m) of token tile I and 32
+// features m.  K stays in registers from its staging and takes the place of A and X
+// once they are operand fragments, so the workgroup needs no more LDS.
+//
+// Bound by memory from dk = 128 (K read, with kWY W written: 36 us for 134 MB at
+// 2048 chunks of dk = 256, 25 us without W); four workgroups per compute unit,
+// which the register bound keeps (136 registers without it).
+template <typename T, int DK, bool kWY>
+__global__ __launch_bounds__(kThreads, 4) void gdn_tri_kernel(const TriArgs a) {
   constexpr int C = kChunk;
   constexpr int P = Pad<T>::value;
   constexpr int LDQ = DK + P;
@@ -49,6 +60,7 @@ __global__ __launch_bounds__(kThreads) void gdn_tri_kernel(const TriArgs a) {
   float* const sX = sA + C * LDA;
   __shared__ __align__(16) float sY[4][16 * 17];
   __shared__ __align__(16) float sGam[C], sBeta[C];
+  __shared__ __align__(16) float sBg[kWY ? C : 4];  // -beta_j e^{gamma_j}
 
   const int N = (a.T + C - 1) / C;
   const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
@@ -86,6 +98,7 @@ __global__ __launch_bounds__(kThreads) void gdn_tri_kernel(const TriArgs a) {
     const float gC = __shfl(x, C - 1);
     sGam[tid] = x;
     sBeta[tid] = bt;
+    if constexpr (kWY) sBg[tid] = -bt * __expf(x);
     float* cf = a.gam + ((size_t)bh * N + ci) * 5 * C + tid;
     cf[0] = x;                      // gamma_j
     // (with raw keys the two coefficients that multiply key rows carry the
@@ -165,15 +178,64 @@ __global__ __launch_bounds__(kThreads) void gdn_tri_kernel(const TriArgs a) {
   // Tm rows i, each 32-column block in acc_pos order: positions 8q .. 8q + 7
   // of a row hold logical columns b + 4 (q % 4) .. + 3 and b + 16 + 4 (q % 4)
   // .. + 3 (b = the block's first column), two 16-byte LDS reads per piece
-  T* Tout = static_cast<T*>(a.Tm) + ((size_t)bh * N + ci) * C * C;
-  for (int idx = tid; idx < C * C / 8; idx += kThreads) {
-    const int i = idx / (C / 8), q = idx % (C / 8);
-    const int lc = ((8 * q) & ~31) + 4 * (q & 3);
-    f32x4 lo = *reinterpret_cast<const f32x4*>(sX + i * LDA + lc);
-    f32x4 hi = *reinterpret_cast<const f32x4*>(sX + i * LDA + lc + 16);
-    if ((lc >> 4) > (i >> 4)) lo = zero4();  // above the diagonal blocks
-    if (((lc + 16) >> 4) > (i >> 4)) hi = zero4();
-    store_acc_pair(Tout + i * C + 8 * q, lo, hi);
+  if (!kWY || a.Tm) {
+    T* Tout = static_cast<T*>(a.Tm) + ((size_t)bh * N + ci) * C * C;
+    for (int idx = tid; idx < C * C / 8; idx += kThreads) {
+      const int i = idx / (C / 8), q = idx % (C / 8);
+      const int lc = ((8 * q) & ~31) + 4 * (q & 3);
+      f32x4 lo = *reinterpret_cast<const f32x4*>(sX + i * LDA + lc);
+      f32x4 hi = *reinterpret_cast<const f32x4*>(sX + i * LDA + lc + 16);
+      if ((lc >> 4) > (i >> 4)) lo = zero4();  // above the diagonal blocks
+      if (((lc + 16) >> 4) > (i >> 4)) hi = zero4();
+      store_acc_pair(Tout + i * C + 8 * q, lo, hi);
+    }
+  }
+
+  if constexpr (kWY) {
+    // lane's entries of block (I, kq): row 16 I + c16, columns
+    // 32 kq + 4 g4 .. + 3 and 32 kq + 16 + 4 g4 .. + 3 (rows of tiles 0 and 1
+    // end in the first block of columns), times the columns' coefficients
+    auto block = [&](int I, int kq, const float* cf) {
+      const int lc = 32 * kq + 4 * g4;
+      f32x4 x = *reinterpret_cast<const f32x4*>(sX + (16 * I + c16) * LDA + lc);
+      f32x4 y = *reinterpret_cast<const f32x4*>(sX + (16 * I + c16) * LDA + lc + 16);
+      x *= *reinterpret_cast<const f32x4*>(cf + lc);
+      y *= *reinterpret_cast<const f32x4*>(cf + lc + 16);
+      if (2 * kq > I) x = zero4();
+      if (2 * kq + 1 > I) y = zero4();
+      return acc_pair_frag<T>(x, y);
+    };
+    T* tb = static_cast<T*>(a.Tb) + ((size_t)bh * N + ci) * (kTbBytes / 2) + 8 * l;
+    const int tb0 = w < 2 ? w : 2 * w - 2;  // (0, 0), (1, 0), (2, 0), (2, 1), (3, 0), (3, 1)
+    store_frag(tb + tb0 * 512, block(w, 0, sBeta));
+    if (w >= 2) store_frag(tb + (tb0 + 1) * 512, block(w, 1, sBeta));
+    Frag<T> tw[4][2];
+#pragma unroll
+    for (int I = 0; I < 4; ++I) {
+      tw[I][0] = block(I, 0, sBg);
+      if (I >= 2) tw[I][1] = block(I, 1, sBg);
+    }
+    __syncthreads();  // A and X are in registers: K takes their place
+    rk.store(sK, LDQ);
+    __syncthreads();
+    T* wout = static_cast<T*>(a.W) + ((size_t)bh * N + ci) * C * DK + 8 * l;
+    for (int m = w; m < DK / 32; m += kThreads / 64) {
+      Frag<T> kf[2][2];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int kq = 0; kq < 2; ++kq) kf[hh][kq] = ld_frag_tr_acc_pair(sK + 32 * kq * LDQ, LDQ, 2 * m + hh);
+#pragma unroll
+      for (int I = 0; I < 4; ++I) {
+        f32x4 x = zero4(), y = zero4();
+#pragma unroll
+        for (int kq = 0; kq < (I >= 2 ? 2 : 1); ++kq) {
+          mma(x, kf[0][kq], tw[I][kq]);
+          mma(y, kf[1][kq], tw[I][kq]);
+        }
+        store_frag(wout + (I * (DK / 32) + m) * 512, acc_pair_frag<T>(x, y));
+      }
+    }
   }
 }
 
@@ -408,13 +470,8 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_state_kernel(const GdnAr
 // unpadded, so K and Tm are stored with their 16-byte pieces permuted per row
 // (an XOR of the piece index) to keep the fragment reads free of bank
 // conflicts: piece p of K row r sits at p ^ kswz(r), of Tm row r at p ^ tswz(r).
-__device__ __forceinline__ int kswz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 __device__ __forceinline__ int tswz(int r) { return (r >> 1) & 7; }
 
-template <int X>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(X) : "memory");
-}
 // s_waitcnt vmcnt(n) for a wave-uniform n in 0..47 (the counter field is an
 // immediate: one scalar branch to the matching wait)
 __device__ __forceinline__ void wait_vm_n(int n) {
@@ -1024,7 +1081,12 @@ hipError_t run_tri(const TriArgs& a, hipStream_t st) {
   const int N = (a.T + kChunk - 1) / kChunk;
   const int nblk = a.B * a.H * N;
   if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL((gdn_tri_kernel<T, DK>), dim3(nblk), dim3(kThreads), 0, st, a);
+  if constexpr (sizeof(T) == 2 && DK >= 128)
+    if (a.W) {
+      hipLaunchKernelGGL((gdn_tri_kernel<T, DK, true>), dim3(nblk), dim3(kThreads), 0, st, a);
+      return hipGetLastError();
+    }
+  hipLaunchKernelGGL((gdn_tri_kernel<T, DK, false>), dim3(nblk), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 template <typename T, int DK, int NPR, int NH>
