@@ -226,12 +226,22 @@ __global__ __launch_bounds__(64 * (DK >= 128 ? 8 : 4), 1) void clean_gram_kernel
 // DECAY: the prefix runs over the segments decayed, X <- E_s X + (segment s's
 // sum, decayed to its end), and the segment's and the earlier tokens' decayed
 // weight sums take the place of the token counts (t0 = 0, no C0 / mu0).
-template <typename T, int DK, bool DECAY>
-__global__ __launch_bounds__(256) void clean_prefix_kernel(const CleanArgs a) {
-  constexpr int PER = DK * DK / 4 / 256;  // workgroups per head
+//
+// With many heads the pass is bound by memory (Grams in, entry moments out: 96 MB
+// in 19 us at 32 heads of dk = 256).  With few heads and many segments a thread's
+// loop over the segments was a chain of round trips and divisions (4 heads of dk
+// = 128, 64 segments: 33 us for 24 MB): there G waves of a workgroup share the
+// same 64 element groups, each taking a G-th of the segments: first their sums,
+// which meet in LDS, then their entry moments from the sum before its own (the
+// Grams again, from the L2).
+template <typename T, int DK, bool DECAY, int G>
+__global__ __launch_bounds__(G == 1 ? 256 : 64 * G) void clean_prefix_kernel(const CleanArgs a) {
+  static_assert(G == 1 || !DECAY, "the decayed sums run in order");
+  constexpr int EPB = G == 1 ? 256 : 64;      // element groups per workgroup
+  constexpr int PER = DK * DK / 4 / EPB;      // workgroups per head
   constexpr int NMT = DK / 16;
   const int bh = blockIdx.x / PER;
-  const int g = (blockIdx.x % PER) * 256 + threadIdx.x;  // element offset / 4
+  const int g = (blockIdx.x % PER) * EPB + threadIdx.x % EPB;  // element offset / 4
   const int l = g & 63, tile = g >> 6;
   const int n = 16 * (tile / NMT) + (l & 15);
   const int m = 16 * (tile % NMT) + 4 * (l >> 4);
@@ -245,7 +255,34 @@ __global__ __launch_bounds__(256) void clean_prefix_kernel(const CleanArgs a) {
   f32x4 run_b = a.mu0 ? *reinterpret_cast<const f32x4*>(a.mu0 + (size_t)bh * DK + m) * t0f : zero4();
   T* Sp = static_cast<T*>(a.sprime);
   float wb = 0.f;  // DECAY: decayed weight of the tokens before segment s
-  for (int s = 0; s < NSL; ++s) {
+  int sbeg = 0, send = NSL;
+  if constexpr (G > 1) {
+    const int w = threadIdx.x >> 6, per = (NSL + G - 1) / G;
+    sbeg = min(NSL, w * per);
+    send = min(NSL, sbeg + per);
+    __shared__ __align__(16) f32x4 sG[G][64], sB[G][64];
+    __shared__ float sA[G][64];
+    f32x4 tg = zero4(), tb = zero4();
+    float ta = 0.f;
+#pragma unroll 4
+    for (int s = sbeg; s < send; ++s) {
+      const size_t so = (size_t)bh * NS + s;
+      tg += *reinterpret_cast<const f32x4*>(a.gram + so * DK * DK + 4 * (size_t)g);
+      tb += *reinterpret_cast<const f32x4*>(a.ssum + so * DK + m);
+      ta += a.ssum[so * DK + n];
+    }
+    sG[w][threadIdx.x & 63] = tg;
+    sB[w][threadIdx.x & 63] = tb;
+    sA[w][threadIdx.x & 63] = ta;
+    __syncthreads();
+    for (int u = 0; u < w; ++u) {
+      acc += sG[u][threadIdx.x & 63];
+      run_b += sB[u][threadIdx.x & 63];
+      run_a += sA[u][threadIdx.x & 63];
+    }
+  }
+#pragma unroll(G == 1 ? 1 : 4)
+  for (int s = sbeg; s < send; ++s) {
     const size_t so = (size_t)bh * NS + s;
     const int cbeg = s * a.seg, cend = min(NCL, cbeg + a.seg);
     float len = (float)(min(sq.len, cend * kChunk) - cbeg * kChunk);
@@ -278,6 +315,9 @@ __global__ __launch_bounds__(256) void clean_prefix_kernel(const CleanArgs a) {
       run_b += tot_b;
     }
   }
+  // the final statistics: by the wave whose segments end the sequence (the first
+  // one where there are none)
+  if (G > 1 && (send != NSL || (sbeg == send && (threadIdx.x >> 6) > 0))) return;
   if (a.t0 + sq.len == 0) {  // no token at all (an empty packed sequence): the initial cache
     if (a.CT)
       *reinterpret_cast<f32x4*>(a.CT + ((size_t)bh * DK + n) * DK + m) =
@@ -871,8 +911,17 @@ hipError_t run_prefix(const CleanArgs& a, hipStream_t st) {
   const long long nblk = (long long)a.B * a.H * (DK * DK / 1024);
   if (nblk == 0) return hipSuccess;
   if (a.la && (a.t0 != 0 || a.C0 || a.mu0 || !a.sdec)) return hipErrorInvalidValue;
-  if (a.la) hipLaunchKernelGGL((clean_prefix_kernel<T, DK, true>), dim3((unsigned)nblk), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((clean_prefix_kernel<T, DK, false>), dim3((unsigned)nblk), dim3(256), 0, st, a);
+  const int ns = n_segs(a.T, a.seg);
+  if (a.la)
+    hipLaunchKernelGGL((clean_prefix_kernel<T, DK, true, 1>), dim3((unsigned)nblk), dim3(256), 0, st, a);
+  // the segments split over waves where the plain form has at most one workgroup
+  // per compute unit (us, split against plain: 4 heads of dk = 128 x 64 segments
+  // 11.4 / 33, 8 fp32 heads of dk = 128 x 8 5.0 / 7.1; but 32 heads of dk = 128 x
+  // 4 13.4 / 8.5, 8 heads of dk = 256 x 32 27.3 / 23.9)
+  else if (ns >= 4 && nblk <= 256)
+    hipLaunchKernelGGL((clean_prefix_kernel<T, DK, false, 8>), dim3((unsigned)nblk * 4), dim3(512), 0, st, a);
+  else
+    hipLaunchKernelGGL((clean_prefix_kernel<T, DK, false, 1>), dim3((unsigned)nblk), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 template <typename T, int DK>
