@@ -2,25 +2,21 @@
 // the l2 normalisation of Q and K and the gate Lambda = sigma(Q W_lambda^T + b_lambda)
 // from the query before the head split; Eq. clean for the gate).
 //
-// Each wave takes four tokens: it requests their whole q and k rows at once
+// Each wave takes TPW tokens (four, or one where there are few): it requests their whole q and k rows at once
 // (16-byte pieces, consecutive lanes along the row), reduces each head's
 // squared norms over the aligned lane group holding that head and writes the
 // normalised pieces; then every gate's partial dot products
 // z[h'] += W[h'][j] q[j] over the lane's pieces, each piece of W read from LDS
-// once for the four tokens; the H partial dots are reduced over the wave and
+// once for the wave's tokens; the H partial dots are reduced over the wave and
 // lane h' writes lambda[h'].  Without output rows (q and k
 // null) the kernel writes the row scales 1 / max(|x|, 1e-12) instead, for a
 // forward that normalises as it stages the raw rows.  W (H x H dk, fp32) is staged
-// in LDS once per workgroup and shared by its 16 tokens.  A wave reads each raw row before it writes the
+// in LDS once per workgroup and shared by its 4 TPW tokens.  A wave reads each raw row before it writes the
 // normalised one, so the outputs may overwrite the inputs.
 #include "ccq_device.h"
 #include "ccq_kernels.h"
 
 namespace ccq {
-
-namespace {
-constexpr int kPrepTokens = 16;  // tokens per workgroup (4 per wave)
-}  // namespace
 
 // Sum over aligned groups of N consecutive lanes (N = 8, 16, 32), every lane
 // receiving its group's sum.
@@ -31,13 +27,37 @@ __device__ __forceinline__ float lane_group_sum(float x) {
   return x;
 }
 
-template <typename T, int DK, int HMAX>
+// A token's row is one long chain (request, norms over lane groups, gates, sums
+// over the wave), so with few tokens a wave's own time is what counts: one token
+// per wave, and the rows requested ahead of the staging of W.
+template <typename T, int DK, int HMAX, int TPW>
 __global__ __launch_bounds__(kThreads) void prep_kernel(const PrepArgs a) {
+  constexpr int kPrepTokens = 4 * TPW;  // tokens per workgroup
   extern __shared__ float sW[];  // [H][H * DK], each row split in half-pieces (below)
   constexpr int PPH = DK / 8;    // 8-element pieces per head row
   constexpr int NPMAX = 4;       // pieces per lane and token (H * DK <= 2048 when supported)
   typedef T v8 __attribute__((ext_vector_type(8)));
   const int H = a.H, E = H * DK, NP = E / 8;
+  const int w = wave_id(), l = lane_id();
+  const long long ntok = (long long)a.B * a.T;
+  const T* qr = static_cast<const T*>(a.q_raw);
+  const T* kr = static_cast<const T*>(a.k_raw);
+  T* qo = static_cast<T*>(a.q);
+  T* ko = static_cast<T*>(a.k);
+  // every piece of the wave's tokens requested first, then W_lambda
+  v8 qa[TPW][NPMAX], ka[TPW][NPMAX];
+#pragma unroll
+  for (int tt = 0; tt < TPW; ++tt) {
+    const long long tok = (long long)blockIdx.x * kPrepTokens + w * TPW + tt;
+#pragma unroll
+    for (int i = 0; i < NPMAX; ++i) {
+      const int p = l + 64 * i;
+      if (tok < ntok && p < NP) {
+        qa[tt][i] = *reinterpret_cast<const v8*>(qr + (size_t)tok * E + 8 * p);
+        ka[tt][i] = *reinterpret_cast<const v8*>(kr + (size_t)tok * E + 8 * p);
+      }
+    }
+  }
   {  // W_lambda into LDS: every 16-byte piece requested before any is stored
     constexpr int NW4 = (int)(kPrepMaxLds / 16 / kThreads);
     const int n4 = H * E / 4;
@@ -60,27 +80,6 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const PrepArgs a) {
     }
   }
   __syncthreads();
-  const int w = wave_id(), l = lane_id();
-  const long long ntok = (long long)a.B * a.T;
-  const T* qr = static_cast<const T*>(a.q_raw);
-  const T* kr = static_cast<const T*>(a.k_raw);
-  T* qo = static_cast<T*>(a.q);
-  T* ko = static_cast<T*>(a.k);
-  constexpr int TPW = kPrepTokens / 4;  // tokens per wave
-  // every piece of the wave's tokens requested first
-  v8 qa[TPW][NPMAX], ka[TPW][NPMAX];
-#pragma unroll
-  for (int tt = 0; tt < TPW; ++tt) {
-    const long long tok = (long long)blockIdx.x * kPrepTokens + w * TPW + tt;
-#pragma unroll
-    for (int i = 0; i < NPMAX; ++i) {
-      const int p = l + 64 * i;
-      if (tok < ntok && p < NP) {
-        qa[tt][i] = *reinterpret_cast<const v8*>(qr + (size_t)tok * E + 8 * p);
-        ka[tt][i] = *reinterpret_cast<const v8*>(kr + (size_t)tok * E + 8 * p);
-      }
-    }
-  }
   // norms of every token's head rows; normalised rows (or the row scales) out
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
@@ -151,10 +150,10 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const PrepArgs a) {
   // butterfly: at each step a lane keeps half of its values, adds its
   // partner's copy of them and hands over the other half, so that after
   // log2(TPW HMAX) steps lane l holds the partial sum of value l % (TPW HMAX)
-  // over the lanes that share its low bits; one more exchange (when 64 lanes
-  // exceed the values) completes the sum
-  constexpr int NZ = TPW * HMAX;  // 64
-  static_assert(NZ == 64, "one value per lane after the butterfly");
+  // over the lanes that share its low bits; where 64 lanes exceed the values,
+  // the exchanges between those lanes complete the sum
+  constexpr int NZ = TPW * HMAX;
+  static_assert(NZ <= 64 && (NZ & (NZ - 1)) == 0, "at most one value per lane after the butterfly");
   float zz[NZ];
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt)
@@ -171,8 +170,10 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const PrepArgs a) {
       zz[j] = mine + __shfl_xor(other, half);
     }
   }
-  // lane l now holds value l (token l / HMAX, gate l % HMAX), summed over the wave
-  {
+#pragma unroll
+  for (int off = NZ; off < 64; off <<= 1) zz[0] += __shfl_xor(zz[0], off);
+  // lane l now holds value l % NZ (token l / HMAX, gate l % HMAX), summed over the wave
+  if (l < NZ) {
     const int tt = l / HMAX, g = l % HMAX;
     const long long tok = (long long)blockIdx.x * kPrepTokens + w * TPW + tt;
     if (g < H && tok < ntok) a.lam[(size_t)tok * H + g] = 1.f / (1.f + __expf(-(zz[0] + a.b[g])));
@@ -184,9 +185,16 @@ template <typename T, int DK>
 hipError_t run_prep(const PrepArgs& a, hipStream_t st) {
   const long long ntok = (long long)a.B * a.T;
   if (ntok == 0 || a.H == 0) return hipSuccess;
-  const unsigned nblk = (unsigned)((ntok + kPrepTokens - 1) / kPrepTokens);
   const size_t lds = (size_t)a.H * a.H * DK * sizeof(float);
-  hipLaunchKernelGGL((prep_kernel<T, DK, kPrepMaxHeads>), dim3(nblk), dim3(kThreads), lds, st, a);
+  // one token per wave while the workgroups of four tokens fit the chip at once
+  // (two per compute unit by the LDS of W_lambda)
+  if (ntok <= 4 * 512) {
+    hipLaunchKernelGGL((prep_kernel<T, DK, kPrepMaxHeads, 1>), dim3((unsigned)((ntok + 3) / 4)), dim3(kThreads), lds, st,
+                       a);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((prep_kernel<T, DK, kPrepMaxHeads, 4>), dim3((unsigned)((ntok + 15) / 16)), dim3(kThreads), lds, st,
+                     a);
   return hipGetLastError();
 }
 template <typename T>
