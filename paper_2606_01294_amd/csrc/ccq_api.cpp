@@ -411,7 +411,7 @@ ccq_status run_forward(ccq_backbone bb, const ccq_shape* s, const void* q, const
 }
 
 // CCQ-Gated DeltaNet training step (arguments validated by the caller).
-ccq_status gdn_fwd_bwd(const ccq_shape* s, const void* q, const void* k, const void* v,
+ccq_status gdn_fwd_bwd(const ccq_shape* s, const int32_t* cu, const void* q, const void* k, const void* v,
                        const float* la, const float* beta, const float* lam, const void* dO,
                        void* o, void* dq, void* dk, void* dv, float* dla, float* dbeta,
                        float* dlam, void* workspace, size_t ws_bytes, void* stream) {
@@ -437,11 +437,14 @@ ccq_status gdn_fwd_bwd(const ccq_shape* s, const void* q, const void* k, const v
   c1.qclean = ws + L.qclean;
   c1.corr = corr;
   c1.mdot = mdq;
+  c1.cu = cu;
   if (run_clean_stats(c1, bf, st) != hipSuccess) return CCQ_ERR_HIP;
   if (traced(st, [&] { return ccq::launch_clean_out(c1, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   ccq::TriArgs ta{k, la, beta, ws + L.Tm, gam, s->B, s->T, s->H, s->dk, s->dv};
+  ta.cu = cu;
   ccq::GdnArgs sa{k, v, beta, ws + L.Tm, gam, nullptr, nullptr, ws + L.states, ws + L.U, s->B,
                   s->T, s->H, s->dk, s->dv};
+  sa.cu = cu;
   const bool wy = use_wy(s, true);
   if (wy) {
     // in buffers that are written after the state pass: W in dS (dv >= 64), Tb in Tm^T
@@ -454,6 +457,7 @@ ccq_status gdn_fwd_bwd(const ccq_shape* s, const void* q, const void* k, const v
     return CCQ_ERR_HIP;
   ccq::GdnOutArgs oa{ws + L.qclean, k, gam, ws + L.states, ws + L.U, o, s->B, s->T, s->H, s->dk,
                      s->dv, s->scale};
+  oa.cu = cu;
   // every S_r is stored (the backward reads them); the output kernel still
   // reads only each group's first and carries S through the group
   oa.group = ccq::gdn_out_group(s->B, s->H, s->T, s->dk, s->dv, bf);
@@ -461,13 +465,16 @@ ccq_status gdn_fwd_bwd(const ccq_shape* s, const void* q, const void* k, const v
   // backward: PT and Tm^T, the reverse state scan, chunk gradients, dq, dk
   ccq::GdnPrepArgs pa{ws + L.qclean, k, gam, ws + L.Tm, ws + L.PT, ws + L.TmT, s->B, s->T, s->H,
                       s->dk, s->dv};
+  pa.cu = cu;
   if (traced(st, [&] { return ccq::launch_gdn_bwd_prep(pa, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   ccq::GdnDstateArgs da{ws + L.qclean, k, dO, gam, ws + L.PT, ws + L.TmT, ws + L.dstates, ws + L.dR,
                         s->B, s->T, s->H, s->dk, s->dv, s->scale};
+  da.cu = cu;
   if (traced(st, [&] { return ccq::launch_gdn_dstate(da, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   ccq::GdnBwdArgs ba{ws + L.qclean, k, v, dO, gam, ws + L.states, ws + L.U, ws + L.dstates,
                      ws + L.dR, corr, dqc, ws + L.dqc_io, dkb, dv, dla, dbeta, dlam, s->B, s->T,
                      s->H, s->dk, s->dv, s->scale};
+  ba.cu = cu;
   if (traced(st, [&] { return ccq::launch_gdn_bwd_chunk(ba, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   ccq::CleanArgs c2 = clean_args(s, ws, L.clean);  // same keys: statistics reused
   c2.q = ws + L.dqc_io;
@@ -476,62 +483,103 @@ ccq_status gdn_fwd_bwd(const ccq_shape* s, const void* q, const void* k, const v
   c2.qclean = dq;
   c2.base = dqc;
   c2.mdot = mdu;
+  c2.cu = cu;
+  c2.back = true;
   if (traced(st, [&] { return ccq::launch_clean_out(c2, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   ccq::CcqDkArgs ka{q, k, ws + L.dqc_io, lam, mdq, mdu, dkb, dk, s->B, s->T, s->H, s->dk,
                     s->centered};
+  ka.cu = cu;
   set_dk_ws(ka, s, ws, L.dkws);
   if (traced(st, [&] { return ccq::launch_ccq_dk(ka, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   return CCQ_OK;
 }
 
-// Padded copies of a packed batch, ahead of the padded path's own workspace.
-struct VarlenLayout {
-  size_t q = 0, k = 0, v = 0, gate = 0, beta = 0, lam = 0, o = 0;
-  size_t dO = 0, dq = 0, dk = 0, dv = 0, dgate = 0, dbeta = 0, dlam = 0;
-  size_t inner = 0, total = 0;
-};
-VarlenLayout varlen_layout(const ccq_shape* s, ccq_backbone bb, bool bwd) {
-  VarlenLayout L;
-  size_t off = 0;
-  auto take = [&](size_t n) {
-    const size_t o = off;
-    off += align_up(n);
-    return o;
-  };
-  const size_t ntok = (size_t)s->B * s->T * s->H, e = esize(s->io_dtype), eg = esize(s->gate_dtype);
-  const size_t gate = bb == CCQ_GLA ? ntok * s->dk * eg : ntok * 4;
-  L.q = take(ntok * s->dk * e);
-  L.k = take(ntok * s->dk * e);
-  L.v = take(ntok * s->dv * e);
-  L.gate = take(gate);
-  if (bb == CCQ_GDN) L.beta = take(ntok * 4);
-  L.lam = take(ntok * 4);
-  L.o = take(ntok * s->dv * e);
-  if (bwd) {
-    L.dO = take(ntok * s->dv * e);
-    L.dq = take(ntok * s->dk * e);
-    L.dk = take(ntok * s->dk * e);
-    L.dv = take(ntok * s->dv * e);
-    L.dgate = take(gate);
-    if (bb == CCQ_GDN) L.dbeta = take(ntok * 4);
-    L.dlam = take(ntok * 4);
-  }
-  L.inner = off;
-  const size_t inner = bwd ? (bb == CCQ_GLA ? bwd_layout(s).total : gdn_bwd_layout(s).total)
-                           : fwd_layout(s, bb).total;
-  L.total = off + inner;
-  return L;
+// CCQ-GLA training step (arguments validated by the caller).
+ccq_status gla_fwd_bwd(const ccq_shape* s, const int32_t* cu, const void* q, const void* k, const void* v,
+                       const void* g_or_logalpha, const float* lam, const void* dO, void* o, void* dq, void* dk,
+                       void* dv, void* dg_or_dlogalpha, float* dlam, void* workspace, size_t ws_bytes,
+                       void* stream) {
+  const bool bf = s->io_dtype == CCQ_BF16;
+  const bool gbf = s->gate_dtype == CCQ_BF16;
+  const BwdLayout L = bwd_layout(s);
+  if (!workspace || ws_bytes < L.total) return CCQ_ERR_WORKSPACE;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  char* ws = static_cast<char*>(workspace);
+  float* corr = reinterpret_cast<float*>(ws + L.corr);
+  float* mdq = reinterpret_cast<float*>(ws + L.mdq);
+  float* mdu = reinterpret_cast<float*>(ws + L.mdu);
+  float* dqc = reinterpret_cast<float*>(ws + L.dqc);
+  float* dkg = reinterpret_cast<float*>(ws + L.dkg);
+  float* db = reinterpret_cast<float*>(ws + L.db);
+  float* dgn = reinterpret_cast<float*>(ws + L.dgn);
+  trace_begin_call();
+
+  // forward: cleaned queries (with Sigma q and m.q kept), then GLA keeping S_r
+  ccq::CleanArgs c1 = clean_args(s, ws, L.clean);
+  c1.q = q;
+  c1.k = k;
+  c1.lam = lam;
+  c1.qclean = ws + L.qclean;
+  c1.corr = corr;
+  c1.mdot = mdq;
+  c1.cu = cu;
+  if (run_clean_stats(c1, bf, st) != hipSuccess) return CCQ_ERR_HIP;
+  if (traced(st, [&] { return ccq::launch_clean_out(c1, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
+  ccq::GlaStateArgs sa{k, v, g_or_logalpha, nullptr, nullptr, ws + L.states, s->B, s->T, s->H,
+                       s->dk, s->dv};
+  sa.cu = cu;
+  if (traced(st, [&] { return ccq::launch_gla_state(sa, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
+  ccq::GlaOutArgs oa{ws + L.qclean, k, v, g_or_logalpha, ws + L.states, o, s->B, s->T, s->H, s->dk,
+                     s->dv, s->scale};
+  oa.cu = cu;
+  // every S_r is stored (the backward reads them); the output kernel still
+  // reads only each group's first and carries S through the group
+  oa.group = ccq::gla_out_group(s->B, s->H, s->T, s->dk, s->dv, bf);
+  if (traced(st, [&] { return ccq::launch_gla_out(oa, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
+  // backward: dS scan, chunk gradients, decay gradient, dq, dk
+  ccq::DstateArgs da{ws + L.qclean, g_or_logalpha, dO, ws + L.dstates, s->B, s->T, s->H, s->dk,
+                     s->dv, s->scale};
+  da.cu = cu;
+  if (traced(st, [&] { return ccq::launch_gla_dstate(da, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
+  ccq::GlaBwdArgs ba{ws + L.qclean, k, v, g_or_logalpha, dO, ws + L.states, ws + L.dstates, corr,
+                     dqc, ws + L.dqc_io, dkg, dv, db, dgn, dlam, s->B, s->T, s->H, s->dk, s->dv,
+                     s->scale};
+  ba.cu = cu;
+  if (traced(st, [&] { return ccq::launch_gla_bwd_chunk(ba, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
+  ccq::DgArgs ga2{db, dgn, dg_or_dlogalpha, s->B, s->T, s->H, s->dk};
+  ga2.cu = cu;
+  if (traced(st, [&] { return ccq::launch_gla_dg(ga2, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
+  ccq::CleanArgs c2 = clean_args(s, ws, L.clean);  // same keys: statistics reused
+  c2.q = ws + L.dqc_io;
+  c2.k = k;
+  c2.lam = lam;
+  c2.qclean = dq;
+  c2.base = dqc;
+  c2.mdot = mdu;
+  c2.cu = cu;
+  c2.back = true;
+  if (traced(st, [&] { return ccq::launch_clean_out(c2, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
+  ccq::CcqDkArgs ka{q, k, ws + L.dqc_io, lam, mdq, mdu, dkg, dk, s->B, s->T, s->H, s->dk,
+                    s->centered};
+  ka.cu = cu;
+  set_dk_ws(ka, s, ws, L.dkws);
+  if (traced(st, [&] { return ccq::launch_ccq_dk(ka, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
+  return CCQ_OK;
 }
 
-// Row bytes of the packed tensors: q/k, v, the gate (GLA [.., dk] in the gate
-// dtype, Gated DeltaNet log alpha [..] fp32) and the per-head scalars.
-struct VarlenRows {
-  size_t qk, v, gate, scalar;
-};
-VarlenRows varlen_rows(const ccq_shape* s, ccq_backbone bb) {
-  const size_t e = esize(s->io_dtype);
-  return {(size_t)s->H * s->dk * e, (size_t)s->H * s->dv * e,
-          bb == CCQ_GLA ? (size_t)s->H * s->dk * esize(s->gate_dtype) : (size_t)s->H * 4, (size_t)s->H * 4};
+// The training step of either backbone on a padded batch (cu null) or a packed
+// one: every kernel reads and writes the caller's packed rows through the
+// offsets and walks only each sequence's own chunks; the workspace's token
+// tensors keep a padded [B, T, ...] layout.
+ccq_status run_fwd_bwd(const ccq_shape* s, ccq_backbone bb, const int32_t* cu, const void* q, const void* k,
+                       const void* v, const void* g_or_logalpha, const float* beta, const float* lam, const void* dO,
+                       void* o, void* dq, void* dk, void* dv, void* dg_or_dlogalpha, float* dbeta, float* dlam,
+                       void* workspace, size_t ws_bytes, void* stream) {
+  if (bb == CCQ_GDN)
+    return gdn_fwd_bwd(s, cu, q, k, v, static_cast<const float*>(g_or_logalpha), beta, lam, dO, o, dq, dk, dv,
+                       static_cast<float*>(dg_or_dlogalpha), dbeta, dlam, workspace, ws_bytes, stream);
+  return gla_fwd_bwd(s, cu, q, k, v, g_or_logalpha, lam, dO, o, dq, dk, dv, dg_or_dlogalpha, dlam, workspace,
+                     ws_bytes, stream);
 }
 
 ccq_status check_varlen(const ccq_shape* s, ccq_backbone bb, const int32_t* cu) {
@@ -615,8 +663,7 @@ extern "C" {
 size_t ccq_varlen_workspace_size(const ccq_shape* s, ccq_backbone bb, int with_bwd) {
   if (check_shape(s, bb) != CCQ_OK) return 0;
   if (with_bwd && !ccq::bwd_supported(s->dk, s->dv, s->io_dtype == CCQ_BF16, bb == CCQ_GDN)) return 0;
-  // the forward reads packed rows directly; the training step runs on padded copies
-  return with_bwd ? varlen_layout(s, bb, true).total : fwd_layout(s, bb).total;
+  return ccq_workspace_size(s, bb, with_bwd);  // every kernel reads the packed rows directly
 }
 
 ccq_status ccq_gla_fwd_varlen(const ccq_shape* s, const int32_t* cu_seqlens, const void* q, const void* k,
@@ -735,9 +782,7 @@ ccq_status ccq_fwd_bwd(const ccq_shape* s, ccq_backbone bb, const void* q, const
   if (rc != CCQ_OK) return rc;
   if (s->t0 != 0) return CCQ_ERR_INVALID_ARG;     // a training step starts from zero states
   if (s->decay_aligned) return CCQ_ERR_UNSUPPORTED;  // the decay-aligned statistics: forward only
-  const bool bf = s->io_dtype == CCQ_BF16;
-  const bool gbf = s->gate_dtype == CCQ_BF16;
-  if (!ccq::bwd_supported(s->dk, s->dv, bf, bb == CCQ_GDN)) return CCQ_ERR_UNSUPPORTED;
+  if (!ccq::bwd_supported(s->dk, s->dv, s->io_dtype == CCQ_BF16, bb == CCQ_GDN)) return CCQ_ERR_UNSUPPORTED;
   const size_t ntok = (size_t)s->B * s->T * s->H;
   if (workspace && !aligned(workspace)) return CCQ_ERR_INVALID_ARG;
   if (ntok > 0) {
@@ -748,65 +793,8 @@ ccq_status ccq_fwd_bwd(const ccq_shape* s, ccq_backbone bb, const void* q, const
       return CCQ_ERR_INVALID_ARG;
   }
   if (ntok == 0) return CCQ_OK;
-  if (bb == CCQ_GDN)
-    return gdn_fwd_bwd(s, q, k, v, static_cast<const float*>(g_or_logalpha), beta, lam, dO, o, dq,
-                       dk, dv, static_cast<float*>(dg_or_dlogalpha), dbeta, dlam, workspace,
-                       ws_bytes, stream);
-  const BwdLayout L = bwd_layout(s);
-  if (!workspace || ws_bytes < L.total) return CCQ_ERR_WORKSPACE;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  char* ws = static_cast<char*>(workspace);
-  float* corr = reinterpret_cast<float*>(ws + L.corr);
-  float* mdq = reinterpret_cast<float*>(ws + L.mdq);
-  float* mdu = reinterpret_cast<float*>(ws + L.mdu);
-  float* dqc = reinterpret_cast<float*>(ws + L.dqc);
-  float* dkg = reinterpret_cast<float*>(ws + L.dkg);
-  float* db = reinterpret_cast<float*>(ws + L.db);
-  float* dgn = reinterpret_cast<float*>(ws + L.dgn);
-  trace_begin_call();
-
-  // forward: cleaned queries (with Sigma q and m.q kept), then GLA keeping S_r
-  ccq::CleanArgs c1 = clean_args(s, ws, L.clean);
-  c1.q = q;
-  c1.k = k;
-  c1.lam = lam;
-  c1.qclean = ws + L.qclean;
-  c1.corr = corr;
-  c1.mdot = mdq;
-  if (run_clean_stats(c1, bf, st) != hipSuccess) return CCQ_ERR_HIP;
-  if (traced(st, [&] { return ccq::launch_clean_out(c1, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  ccq::GlaStateArgs sa{k, v, g_or_logalpha, nullptr, nullptr, ws + L.states, s->B, s->T, s->H,
-                       s->dk, s->dv};
-  if (traced(st, [&] { return ccq::launch_gla_state(sa, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  ccq::GlaOutArgs oa{ws + L.qclean, k, v, g_or_logalpha, ws + L.states, o, s->B, s->T, s->H, s->dk,
-                     s->dv, s->scale};
-  // every S_r is stored (the backward reads them); the output kernel still
-  // reads only each group's first and carries S through the group
-  oa.group = ccq::gla_out_group(s->B, s->H, s->T, s->dk, s->dv, bf);
-  if (traced(st, [&] { return ccq::launch_gla_out(oa, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  // backward: dS scan, chunk gradients, decay gradient, dq, dk
-  ccq::DstateArgs da{ws + L.qclean, g_or_logalpha, dO, ws + L.dstates, s->B, s->T, s->H, s->dk,
-                     s->dv, s->scale};
-  if (traced(st, [&] { return ccq::launch_gla_dstate(da, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  ccq::GlaBwdArgs ba{ws + L.qclean, k, v, g_or_logalpha, dO, ws + L.states, ws + L.dstates, corr,
-                     dqc, ws + L.dqc_io, dkg, dv, db, dgn, dlam, s->B, s->T, s->H, s->dk, s->dv,
-                     s->scale};
-  if (traced(st, [&] { return ccq::launch_gla_bwd_chunk(ba, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  ccq::DgArgs ga2{db, dgn, dg_or_dlogalpha, s->B, s->T, s->H, s->dk};
-  if (traced(st, [&] { return ccq::launch_gla_dg(ga2, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  ccq::CleanArgs c2 = clean_args(s, ws, L.clean);  // same keys: statistics reused
-  c2.q = ws + L.dqc_io;
-  c2.k = k;
-  c2.lam = lam;
-  c2.qclean = dq;
-  c2.base = dqc;
-  c2.mdot = mdu;
-  if (traced(st, [&] { return ccq::launch_clean_out(c2, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  ccq::CcqDkArgs ka{q, k, ws + L.dqc_io, lam, mdq, mdu, dkg, dk, s->B, s->T, s->H, s->dk,
-                    s->centered};
-  set_dk_ws(ka, s, ws, L.dkws);
-  if (traced(st, [&] { return ccq::launch_ccq_dk(ka, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  return CCQ_OK;
+  return run_fwd_bwd(s, bb, nullptr, q, k, v, g_or_logalpha, beta, lam, dO, o, dq, dk, dv, dg_or_dlogalpha, dbeta,
+                     dlam, workspace, ws_bytes, stream);
 }
 
 ccq_status ccq_fwd_bwd_varlen(const ccq_shape* s, ccq_backbone bb, const int32_t* cu_seqlens, const void* q,
@@ -825,32 +813,8 @@ ccq_status ccq_fwd_bwd_varlen(const ccq_shape* s, ccq_backbone bb, const int32_t
   for (const void* p : req)
     if (!p || !aligned(p)) return CCQ_ERR_INVALID_ARG;
   if (bb == CCQ_GDN && (!beta || !aligned(beta) || !dbeta || !aligned(dbeta))) return CCQ_ERR_INVALID_ARG;
-  const VarlenLayout L = varlen_layout(s, bb, true);
-  if (!workspace || ws_bytes < L.total) return CCQ_ERR_WORKSPACE;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  char* ws = static_cast<char*>(workspace);
-  const VarlenRows R = varlen_rows(s, bb);
-  const int32_t* cu = cu_seqlens;
-  TraceScope scope;
-  auto copy = [&](void* dst, const void* src, size_t rb, bool to_padded) {
-    return traced(st, [&] { return ccq::launch_varlen_copy(dst, src, cu, s->B, s->T, rb, to_padded, st); }) ==
-           hipSuccess;
-  };
-  if (!copy(ws + L.q, q, R.qk, true) || !copy(ws + L.k, k, R.qk, true) || !copy(ws + L.v, v, R.v, true) ||
-      !copy(ws + L.gate, g_or_logalpha, R.gate, true) || (bb == CCQ_GDN && !copy(ws + L.beta, beta, R.scalar, true)) ||
-      !copy(ws + L.lam, lam, R.scalar, true) || !copy(ws + L.dO, dO, R.v, true))
-    return CCQ_ERR_HIP;
-  rc = ccq_fwd_bwd(s, bb, ws + L.q, ws + L.k, ws + L.v, ws + L.gate,
-                   bb == CCQ_GDN ? reinterpret_cast<const float*>(ws + L.beta) : nullptr,
-                   reinterpret_cast<const float*>(ws + L.lam), ws + L.dO, ws + L.o, ws + L.dq, ws + L.dk,
-                   ws + L.dv, ws + L.dgate, bb == CCQ_GDN ? reinterpret_cast<float*>(ws + L.dbeta) : nullptr,
-                   reinterpret_cast<float*>(ws + L.dlam), ws + L.inner, ws_bytes - L.inner, stream);
-  if (rc != CCQ_OK) return rc;
-  if (!copy(o, ws + L.o, R.v, false) || !copy(dq, ws + L.dq, R.qk, false) || !copy(dk, ws + L.dk, R.qk, false) ||
-      !copy(dv, ws + L.dv, R.v, false) || !copy(dg_or_dlogalpha, ws + L.dgate, R.gate, false) ||
-      (bb == CCQ_GDN && !copy(dbeta, ws + L.dbeta, R.scalar, false)) || !copy(dlam, ws + L.dlam, R.scalar, false))
-    return CCQ_ERR_HIP;
-  return CCQ_OK;
+  return run_fwd_bwd(s, bb, cu_seqlens, q, k, v, g_or_logalpha, beta, lam, dO, o, dq, dk, dv, dg_or_dlogalpha, dbeta,
+                     dlam, workspace, ws_bytes, stream);
 }
 
 // Decode workspace: Cbar_t q [B,H,dk] fp32 when the step is split into two

@@ -81,8 +81,10 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
   const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
   const int bh = lb / N, ci = lb % N;
   const int b = bh / a.H, h = bh % a.H;
+  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
   const int r0 = ci * C;
-  const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
+  if (r0 >= sq.len) return;  // past a packed sequence's end
+  const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = lane_id();
   const int sw = w & 3, hh = w >> 2;  // stripe, half (uniform)
   const int ct0 = hh * NTW;           // this wave's first key-channel tile
@@ -102,9 +104,9 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
     typedef RowTile<T, DK, NT> TileQ;
     TileQ rq, rk;
     RowTile<TG, DK, NT> rg;
-    rq.load(qc + tok_off(b, r0, h, a.T, a.H, DK), gsk, nrow);
-    rk.load(k + tok_off(b, r0, h, a.T, a.H, DK), gsk, nrow);
-    rg.load(gate + tok_off(b, r0, h, a.T, a.H, DK), gsk, nrow);
+    rq.load(qc + seq_off(sp, r0, h, a.H, DK), gsk, nrow);
+    rk.load(k + seq_off(sq, r0, h, a.H, DK), gsk, nrow);
+    rg.load(gate + seq_off(sq, r0, h, a.H, DK), gsk, nrow);
     rg.store_f32(sG, LDG);
     lds_barrier();
     if (tid < DK) {
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
   for (int ct = 0; ct < NTW; ++ct) { X1[ct] = zero4(); X2[ct] = zero4(); }
 #pragma unroll
   for (int J = 0; J < 4; ++J) Adv[J] = zero4();
-  T* dvrow = static_cast<T*>(a.dv_out) + tok_off(b, r0, h, a.T, a.H, a.dv);
+  T* dvrow = static_cast<T*>(a.dv_out) + seq_off(sq, r0, h, a.H, a.dv);
   // every value slice's global operands are requested one slice ahead
   typedef T v8 __attribute__((ext_vector_type(8)));
   constexpr int NPS = BV * DK / 8 / NT;  // 8-element pieces of S_r (and dS) per thread
@@ -173,8 +175,8 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
       sl.s[p] = *reinterpret_cast<const v8*>(Sst + (size_t)(vv0 + row) * DK + c0);
       sl.d[p] = *reinterpret_cast<const v8*>(dSst + (size_t)(vv0 + row) * DK + c0);
     }
-    sl.rv.load(v + tok_off(b, r0, h, a.T, a.H, a.dv) + vv0, gsv, nrow);
-    sl.rdo.load(dO + tok_off(b, r0, h, a.T, a.H, a.dv) + vv0, gsv, nrow);
+    sl.rv.load(v + seq_off(sq, r0, h, a.H, a.dv) + vv0, gsv, nrow);
+    sl.rdo.load(dO + seq_off(sq, r0, h, a.H, a.dv) + vv0, gsv, nrow);
   };
   Slice cur;
   load_slice(cur, 0);
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
   // ---- phase 4: epilogue per element (row i of stripe sw, key channel c)
   // every global operand of the epilogue requested at once (rows clamped into
   // the sequence), then the per-element arithmetic
-  const size_t rowoff = tok_off(b, r0, h, a.T, a.H, DK);
+  const size_t rowoff = seq_off(sp, r0, h, a.H, DK), keyoff = seq_off(sq, r0, h, a.H, DK);
   T* dqc_io = static_cast<T*>(a.dqc_io) + rowoff;
   float* dqc_f = a.dqc + rowoff;
   float* dkg_f = a.dk_gla + rowoff;
@@ -269,7 +271,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
       const int i = 16 * sw + 4 * g4 + r;
       const int off = (i < nrow ? i : nrow - 1) * (int)gsk + 16 * (ct0 + ct) + c16;
       qv[ct][r] = f32(qc[rowoff + off]);
-      kv[ct][r] = f32(k[rowoff + off]);
+      kv[ct][r] = f32(k[keyoff + off]);
       cv[ct][r] = a.corr[rowoff + off];
     }
   float kdk[NTW];  // sum over the chunk's rows of k * dk^inter
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = 16 * sw + 4 * g4 + r;
-      if (c16 == 0 && i < nrow) a.dlam[((size_t)b * a.T + r0 + i) * a.H + h] = dl[r];
+      if (c16 == 0 && i < nrow) a.dlam[seq_idx(sq, r0 + i, h, a.H)] = dl[r];
     }
   // decay gradient at the next chunk's first token:
   //   e^{b_C} sum_v S_r dS_{r+1} + sum_j k_j * dk_j^inter
@@ -360,11 +362,13 @@ __global__ __launch_bounds__(kThreads) void gla_dg_kernel(const DgArgs a) {
   const int lb = blockIdx.x;
   const int bh = lb / N, ci = lb % N;
   const int b = bh / a.H, h = bh % a.H;
+  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
   const int r0 = ci * C;
-  const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
+  if (r0 >= sq.len) return;  // past a packed sequence's end
+  const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
   const int hd = a.H * a.dk;
-  TG* dg = static_cast<TG*>(a.dg) + tok_off(b, r0, h, a.T, a.H, a.dk);
-  const float* db = a.db + tok_off(b, r0, h, a.T, a.H, a.dk);
+  TG* dg = static_cast<TG*>(a.dg) + seq_off(sq, r0, h, a.H, a.dk);
+  const float* db = a.db + seq_off(sp, r0, h, a.H, a.dk);
   // thread (c, half): half 1 takes rows 32..63 of channel c, half 0 rows 0..31
   const int npc = kThreads / 2;  // channels per pass
   for (int c0 = 0; c0 < a.dk; c0 += npc) {
@@ -437,6 +441,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_stats_kernel(const CcqDkAr
   const int split = lbs % NSPLIT, lb = lbs / NSPLIT;  // split: this workgroup's share of the tiles
   const int bh = lb / NS, sg = lb % NS;
   const int b = bh / a.H, h = bh % a.H;
+  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
   const int tid = threadIdx.x, w = wave_id(), l = lane_id();
   const int g4 = l >> 4, c16 = l & 15;
   const int tw0 = (split * NWV + w) * NPW;  // first tile of this wave
@@ -444,7 +449,9 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_stats_kernel(const CcqDkAr
   const T* uu = static_cast<const T*>(a.u);
   const size_t gs = (size_t)a.H * DK;
   const int c_begin = sg * a.seg;
-  const int c_end = (c_begin + a.seg) < N ? (c_begin + a.seg) : N;
+  // (none past a packed sequence's end: the segment's H and D are then zero)
+  const int NL = (sq.len + C - 1) / C;
+  const int c_end = (c_begin + a.seg) < NL ? (c_begin + a.seg) : NL;
 
   f32x4 H[NPW];
 #pragma unroll
@@ -456,15 +463,15 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_stats_kernel(const CcqDkAr
   RowScalar rlam, rmq, rmu;   // wave 0: lane = row
   auto prefetch = [&](int ci) {
     const int r0 = ci * C;
-    const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
-    rq.load(q + tok_off(b, r0, h, a.T, a.H, DK), gs, nrow);
-    ru.load(uu + tok_off(b, r0, h, a.T, a.H, DK), gs, nrow);
-    const size_t t0i = ((size_t)b * a.T + r0) * a.H + h;
-    fl.load(a.lam + t0i, (size_t)a.H, nrow);
+    const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
+    rq.load(q + seq_off(sq, r0, h, a.H, DK), gs, nrow);
+    ru.load(uu + seq_off(sp, r0, h, a.H, DK), gs, nrow);
+    const size_t ti = seq_idx(sq, r0, h, a.H), tp = seq_idx(sp, r0, h, a.H);
+    fl.load(a.lam + ti, (size_t)a.H, nrow);
     if (w == 0) {
-      rlam.load(a.lam + t0i, (size_t)a.H, l, nrow);
-      rmq.load(a.mdot_q + t0i, (size_t)a.H, l, nrow);
-      rmu.load(a.mdot_u + t0i, (size_t)a.H, l, nrow);
+      rlam.load(a.lam + ti, (size_t)a.H, l, nrow);
+      rmq.load(a.mdot_q + tp, (size_t)a.H, l, nrow);
+      rmu.load(a.mdot_u + tp, (size_t)a.H, l, nrow);
     }
   };
   if (c_begin < c_end) prefetch(c_begin);
@@ -590,6 +597,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
   const int split = lbs % NSPLIT, lb = lbs / NSPLIT;
   const int bh = lb / NS, sg = lb % NS;
   const int b = bh / a.H, h = bh % a.H;
+  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
   const int tid = threadIdx.x, w = wave_id(), l = lane_id();
   const int g4 = l >> 4, c16 = l & 15;
   const int nt0 = (split * NWV + w) * NTW;  // first output column tile of this wave
@@ -599,7 +607,9 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
   T* dk_out = static_cast<T*>(a.dk_out);
   const size_t gs = (size_t)a.H * DK;
   const int c_begin = sg * a.seg;
-  const int c_end = (c_begin + a.seg) < N ? (c_begin + a.seg) : N;
+  // (none past a packed sequence's end: the segment's H and D are then zero)
+  const int NL = (sq.len + C - 1) / C;
+  const int c_end = (c_begin + a.seg) < NL ? (c_begin + a.seg) : NL;
 
   // the weights' tiles above the diagonal stay zero
   for (int idx = tid; idx < C * LDA; idx += NTHR) {
@@ -637,7 +647,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
   RowScalar rlam, rmq, rmu;   // wave 0: lane = row
   auto prefetch = [&](int ci) {
     const int r0 = ci * C;
-    const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
+    const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
     // (at DK = 256 with the row offsets formed at the loads: fewer registers
     // held across the chunk loop, less spill; measured 437 -> 426 us there,
     // slightly slower at DK = 128)
@@ -645,22 +655,22 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
       if constexpr (DK >= 256) t.load_opaque(src, gs, nrow);
       else t.load(src, gs, nrow);
     };
-    ld(rq, q + tok_off(b, r0, h, a.T, a.H, DK));
-    ld(ru, uu + tok_off(b, r0, h, a.T, a.H, DK));
-    ld(rk, k + tok_off(b, r0, h, a.T, a.H, DK));
-    const size_t t0i = ((size_t)b * a.T + r0) * a.H + h;
-    fl.load(a.lam + t0i, (size_t)a.H, nrow);
+    ld(rq, q + seq_off(sq, r0, h, a.H, DK));
+    ld(ru, uu + seq_off(sp, r0, h, a.H, DK));
+    ld(rk, k + seq_off(sq, r0, h, a.H, DK));
+    const size_t ti = seq_idx(sq, r0, h, a.H), tp = seq_idx(sp, r0, h, a.H);
+    fl.load(a.lam + ti, (size_t)a.H, nrow);
     if (w == 0) {
-      rlam.load(a.lam + t0i, (size_t)a.H, l, nrow);
-      rmq.load(a.mdot_q + t0i, (size_t)a.H, l, nrow);
-      rmu.load(a.mdot_u + t0i, (size_t)a.H, l, nrow);
+      rlam.load(a.lam + ti, (size_t)a.H, l, nrow);
+      rmq.load(a.mdot_q + tp, (size_t)a.H, l, nrow);
+      rmu.load(a.mdot_u + tp, (size_t)a.H, l, nrow);
     }
   };
   if (c_begin < c_end) prefetch(c_end - 1);
 
   for (int ci = c_end - 1; ci >= c_begin; --ci) {
     const int r0 = ci * C;
-    const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
+    const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
     lds_barrier();  // (A)
     {
       if (w == 0) {
@@ -689,7 +699,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
     // the backbone's part of dk for this wave's outputs, requested before the
     // products: here at DK = 256 (fewer registers live in the dk-row products),
     // else at the start of those products (measured faster there)
-    const size_t rowoff = tok_off(b, r0, h, a.T, a.H, DK);
+    const size_t rowoff = seq_off(sp, r0, h, a.H, DK), outoff = seq_off(sq, r0, h, a.H, DK);
     constexpr bool kEarlyDkg = DK >= 256;
     float dkg[NTW][4][4];
     auto load_dkg = [&](int x) {
@@ -798,7 +808,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
         for (int r = 0; r < 4; ++r) {
           const int jr = 16 * J + 4 * g4 + r;
           if (jr < nrow) {
-            dk_out[rowoff + jr * (int)gs + 16 * nt + c16] = to<T>(dkg[x][J][r] + acc[J][r] + dreg[x]);
+            dk_out[outoff + jr * (int)gs + 16 * nt + c16] = to<T>(dkg[x][J][r] + acc[J][r] + dreg[x]);
           }
         }
       }

@@ -420,10 +420,12 @@ __global__ __launch_bounds__(64 * NW, 1) void clean_out_kernel(const CleanArgs a
   const int bh = lb / NS, s = lb % NS;
   const int b = bh / a.H, h = bh % a.H;
   const Seq sq = seq_of(a.cu, b, a.T);
-  // rows of the token tensors this kernel writes (q_clean and, in training,
-  // Sigma x, m . x and the base), which live in the workspace in a padded
-  // [B, T, ...] layout whatever the layout of the inputs
-  const Seq sw{(long long)b * a.T, sq.len};
+  // The workspace's token tensors are padded [B, T, ...] whatever the caller's
+  // layout: in a forward the rows this kernel writes (q_clean and, in training,
+  // Sigma x and m . x); in the dq pass (a.back) x, the base and m . x, while the
+  // output dq is the caller's
+  const Seq sw = padded_rows(sq, b, a.T);
+  const Seq srx = a.back ? sw : sq, sro = a.back ? sq : sw;
   const int cbeg = s * a.seg, cend = min(n_chunks(sq.len), cbeg + a.seg);
   if (cbeg >= cend) return;  // a segment past a packed sequence's end
   const int tid = threadIdx.x;
@@ -446,7 +448,7 @@ __global__ __launch_bounds__(64 * NW, 1) void clean_out_kernel(const CleanArgs a
   auto stream_piece = [&](int c, int i) {
     if constexpr (kDma) {
       const int r0 = c * C, n = min(C, sq.len - r0);
-      if (i < Stream::NI) Stream::load_one(x + seq_off(sq, r0, h, a.H, DK), gstride, n, sSt, i);
+      if (i < Stream::NI) Stream::load_one(x + seq_off(srx, r0, h, a.H, DK), gstride, n, sSt, i);
       else Stream::load_one(k + seq_off(sq, r0, h, a.H, DK), gstride, n, sSt + C * DK, i - Stream::NI);
     }
   };
@@ -467,7 +469,7 @@ __global__ __launch_bounds__(64 * NW, 1) void clean_out_kernel(const CleanArgs a
 #pragma unroll
         for (int i = 0; i < 2 * Stream::NI; ++i) stream_piece(c, i);
     } else {
-      rx.load(x + seq_off(sq, r0, h, a.H, DK), gstride, n);
+      rx.load(x + seq_off(srx, r0, h, a.H, DK), gstride, n);
       rk.load(k + seq_off(sq, r0, h, a.H, DK), gstride, n);
     }
     if (tid < C) rl.load(a.lam + seq_idx(sq, r0, h, a.H), (size_t)a.H, tid, n);
@@ -590,7 +592,7 @@ __global__ __launch_bounds__(64 * NW, 1) void clean_out_kernel(const CleanArgs a
         for (int u = 0; u < NV; ++u) qo[u] = *reinterpret_cast<const vec_t*>(sX + ((t_ + NT * u) / VPR) * LDK + col);
 #pragma unroll
         for (int u = 0; u < NV; ++u)
-          *reinterpret_cast<vec_t*>(qc + seq_off(sw, r0 - C + (t_ + NT * u) / VPR, h, a.H, DK) + col) = qo[u];
+          *reinterpret_cast<vec_t*>(qc + seq_off(sro, r0 - C + (t_ + NT * u) / VPR, h, a.H, DK) + col) = qo[u];
       }
       if constexpr (kDma) take();
       auto put = [&](auto masked) {
@@ -884,7 +886,7 @@ __global__ __launch_bounds__(64 * NW, 1) void clean_out_kernel(const CleanArgs a
     for (int u = 0; u < NV; ++u) {
       const int e = tid + NT * u, row = e / VPR, col = (e % VPR) * 8;
       if (row < nrow)
-        *reinterpret_cast<vec_t*>(qc + seq_off(sw, r0 + row, h, a.H, DK) + col) =
+        *reinterpret_cast<vec_t*>(qc + seq_off(sro, r0 + row, h, a.H, DK) + col) =
             *reinterpret_cast<const vec_t*>(sX + row * LDK + col);
     }
   }

@@ -723,6 +723,9 @@ __device__ __forceinline__ Seq seq_of(const int* cu, int b, int T) {
   len = len < 0 ? 0 : (len > T ? T : len);
   return Seq{(long long)cu[b], len};
 }
+// The same sequence in the workspace's token tensors, which are padded
+// [B, T, ...] whatever the caller's layout.
+__device__ __forceinline__ Seq padded_rows(const Seq& q, int b, int T) { return Seq{(long long)b * T, q.len}; }
 // Offset of token t of sequence q, head h, in a [rows, H, D] tensor (elements).
 __device__ __forceinline__ size_t seq_off(const Seq& q, int t, int h, int H, int D) {
   return ((size_t)(q.row0 + t) * H + h) * (size_t)D;

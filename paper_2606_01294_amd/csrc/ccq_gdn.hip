@@ -935,7 +935,7 @@ __global__ __launch_bounds__(kOutThreads, 1) void gdn_out_kernel(const GdnOutArg
     const bool carry = CARRY && ci + 1 < ce;
     {
       RowTile<T, DK, kOutThreads> rq, rk;
-      rq.load(static_cast<const T*>(a.qc) + seq_off(Seq{(long long)b * a.T, sq.len}, r0, h, a.H, DK), gstride,
+      rq.load(static_cast<const T*>(a.qc) + seq_off(padded_rows(sq, b, a.T), r0, h, a.H, DK), gstride,
               nrow);  // q_clean: the workspace's padded rows
       rk.load(static_cast<const T*>(a.k) + seq_off(sq, r0, h, a.H, DK), gstride, nrow);
       const float* gm = a.gam + ((size_t)bh * N + ci) * 5 * C;

@@ -49,16 +49,18 @@ __global__ __launch_bounds__(kThreads) void gdn_bwd_prep_kernel(const GdnPrepArg
   const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
   const int bh = lb / N, ci = lb % N;
   const int b = bh / a.H, h = bh % a.H;
+  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
   const int r0 = ci * C;
-  const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
+  if (r0 >= sq.len) return;  // past a packed sequence's end
+  const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
   const int tid = threadIdx.x, w = wave_id(), l = lane_id();
   const int g4 = l >> 4, c16 = l & 15;
   const size_t cidx = (size_t)bh * N + ci;
   {
     RowTile<T, DK> rq, rk;
     RowTile<T, C> rt;
-    rq.load(static_cast<const T*>(a.qc) + tok_off(b, r0, h, a.T, a.H, DK), (size_t)a.H * DK, nrow);
-    rk.load(static_cast<const T*>(a.k) + tok_off(b, r0, h, a.T, a.H, DK), (size_t)a.H * DK, nrow);
+    rq.load(static_cast<const T*>(a.qc) + seq_off(sp, r0, h, a.H, DK), (size_t)a.H * DK, nrow);
+    rk.load(static_cast<const T*>(a.k) + seq_off(sq, r0, h, a.H, DK), (size_t)a.H * DK, nrow);
     rt.load(static_cast<const T*>(a.Tm) + cidx * C * C, (size_t)C, C);
     if (tid < C) sGam[tid] = a.gam[cidx * 5 * C + tid];
     rq.store(sQ, LDQ);
@@ -135,6 +137,8 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnD
   const int bh = lb / nvt;
   const int v0 = (lb % nvt) * BVS;
   const int b = bh / a.H, h = bh % a.H;
+  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
+  const int NL = (sq.len + C - 1) / C;  // chunks walked (a packed sequence's own)
   const int tid = threadIdx.x, w = wave_id(), l = lane_id();
   const int pr = w / NH, hq = w % NH;
   const int g4 = l >> 4, c16 = l & 15;
@@ -169,17 +173,17 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnD
   // points of the previous chunk so that their issue overlaps its products
   auto prefetch_kq = [&](int ci) {
     const int r0 = ci * C;
-    const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
-    st.rk.load(k + tok_off(b, r0, h, a.T, a.H, DK), (size_t)a.H * DK, nrow);
-    st.rq.load(qc + tok_off(b, r0, h, a.T, a.H, DK), (size_t)a.H * DK, nrow);
+    const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
+    st.rk.load(k + seq_off(sq, r0, h, a.H, DK), (size_t)a.H * DK, nrow);
+    st.rq.load(qc + seq_off(sp, r0, h, a.H, DK), (size_t)a.H * DK, nrow);
   };
   auto prefetch = [&](int ci) {
     const int r0 = ci * C;
-    const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
+    const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
     const size_t cidx = (size_t)bh * N + ci;
     st.rp.load(static_cast<const T*>(a.PT) + cidx * C * C, (size_t)C, C);
     st.rt.load(static_cast<const T*>(a.TmT) + cidx * C * C, (size_t)C, C);
-    if (tid < NTO) st.rdo.load(dO + tok_off(b, r0, h, a.T, a.H, a.dv) + v0, (size_t)a.H * a.dv, nrow);
+    if (tid < NTO) st.rdo.load(dO + seq_off(sq, r0, h, a.H, a.dv) + v0, (size_t)a.H * a.dv, nrow);
     if constexpr (kRowQ) {
 #pragma unroll
       for (int u = 0; u < NGQ; ++u) st.gq[u] = a.gam[cidx * 5 * C + RowTile<T, DK, NT>::row(u)];
@@ -192,14 +196,14 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnD
       st.cf[2].load(a.gam + (cidx * 5 + 4) * C, 1, tid, C);
     }
   };
-  if (N > 0) {
-    prefetch_kq(N - 1);
-    prefetch(N - 1);
+  if (NL > 0) {
+    prefetch_kq(NL - 1);
+    prefetch(NL - 1);
   }
 
-  for (int ci = N - 1; ci >= 0; --ci) {
+  for (int ci = NL - 1; ci >= 0; --ci) {
     const int r0 = ci * C;
-    const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
+    const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
     const size_t cidx = (size_t)bh * N + ci;
     lds_barrier();  // every wave is done with the previous chunk's LDS
     st.rk.store(sK, LDQ);
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnD
       mma(dU[I], ld_frag(sPT + 16 * I * LDP, LDP), of0);
       mma(dU[I], ld_frag(sPT + 16 * I * LDP + 32, LDP), of1);
     }
-    T* dRrow = dRg + tok_off(b, r0, h, a.T, a.H, a.dv) + v;
+    T* dRrow = dRg + seq_off(sp, r0, h, a.H, a.dv) + v;
     // dR = Tm^T dU
     const Frag<T> uf0 = acc_pair_frag<T>(dU[0], dU[1]);
     const Frag<T> uf1 = acc_pair_frag<T>(dU[2], dU[3]);
@@ -356,8 +360,10 @@ __global__ __launch_bounds__(64 * NW, 1) void gdn_bwd_chunk_kernel(const GdnBwdA
   const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
   const int bh = lb / N, ci = lb % N;
   const int b = bh / a.H, h = bh % a.H;
+  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
   const int r0 = ci * C;
-  const int nrow = (a.T - r0) < C ? (a.T - r0) : C;
+  if (r0 >= sq.len) return;  // past a packed sequence's end
+  const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = lane_id();
   const int sw = w & 3, hh = w >> 2;  // stripe, half (uniform)
   const int ct0 = hh * NTW;           // this wave's first key-channel tile
@@ -370,8 +376,8 @@ __global__ __launch_bounds__(64 * NW, 1) void gdn_bwd_chunk_kernel(const GdnBwdA
   f32x4 QK[NJ], KK[NJ];
   {
     ChunkTile<T, DK, NT> rq, rk;
-    rq.load(static_cast<const T*>(a.qc) + tok_off(b, r0, h, a.T, a.H, DK), gsk, nrow);
-    rk.load(static_cast<const T*>(a.k) + tok_off(b, r0, h, a.T, a.H, DK), gsk, nrow);
+    rq.load(static_cast<const T*>(a.qc) + seq_off(sp, r0, h, a.H, DK), gsk, nrow);
+    rk.load(static_cast<const T*>(a.k) + seq_off(sq, r0, h, a.H, DK), gsk, nrow);
     if (tid < C) {
       sGam[tid] = a.gam[cidx * 5 * C + tid];
       sBeta[tid] = a.gam[(cidx * 5 + 2) * C + tid];
@@ -413,7 +419,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gdn_bwd_chunk_kernel(const GdnBwdA
     const T* Sg = static_cast<const T*>(a.states) + cidx * a.dv * DK;
     const T* Ug = static_cast<const T*>(a.U) + cidx * a.dv * C;
     const T* Dg = static_cast<const T*>(a.dstates) + cidx * a.dv * DK;
-    T* dvrow = static_cast<T*>(a.dv_out) + tok_off(b, r0, h, a.T, a.H, a.dv);
+    T* dvrow = static_cast<T*>(a.dv_out) + seq_off(sq, r0, h, a.H, a.dv);
     typedef T v8 __attribute__((ext_vector_type(8)));
     // every value slice's global operands are requested one slice ahead
     constexpr int NPS = BV * DK / 8 / NT;              // pieces of S_r and of D per thread
@@ -443,9 +449,9 @@ __global__ __launch_bounds__(64 * NW, 1) void gdn_bwd_chunk_kernel(const GdnBwdA
           sl.u[p] = *reinterpret_cast<const v8*>(Ug + (size_t)(vv0 / 16 + vt) * 16 * C + (size_t)(m * 16 + vr) * 32 + 8 * pp);
         }
       }
-      sl.rdo.load(static_cast<const T*>(a.dO) + tok_off(b, r0, h, a.T, a.H, a.dv) + vv0, gsv, nrow);
-      sl.rdr.load(static_cast<const T*>(a.dR) + tok_off(b, r0, h, a.T, a.H, a.dv) + vv0, gsv, nrow);
-      sl.rvv.load(static_cast<const T*>(a.v) + tok_off(b, r0, h, a.T, a.H, a.dv) + vv0, gsv, nrow);
+      sl.rdo.load(static_cast<const T*>(a.dO) + seq_off(sq, r0, h, a.H, a.dv) + vv0, gsv, nrow);
+      sl.rdr.load(static_cast<const T*>(a.dR) + seq_off(sp, r0, h, a.H, a.dv) + vv0, gsv, nrow);
+      sl.rvv.load(static_cast<const T*>(a.v) + seq_off(sq, r0, h, a.H, a.dv) + vv0, gsv, nrow);
     };
     Slice cur;
     load_slice(cur, 0);
@@ -525,7 +531,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gdn_bwd_chunk_kernel(const GdnBwdA
   if (VTile::mine(0) && (tid & 3) == 0) sRV[vrow] = rv;
 
   // Sigma_t q_t for this wave's rows, requested now for the epilogue
-  const size_t rowoff = tok_off(b, r0, h, a.T, a.H, DK);
+  const size_t rowoff = seq_off(sp, r0, h, a.H, DK);
   float cr[NTW][4];
 #pragma unroll
   for (int ct = 0; ct < NTW; ++ct)
@@ -659,7 +665,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gdn_bwd_chunk_kernel(const GdnBwdA
         sDg[i] = i < nrow ? dg : 0.f;
         xt += i < nrow ? sDec[i] * d3[r] : 0.f;
         if (i < nrow) {
-          const size_t ti = ((size_t)b * a.T + r0 + i) * a.H + h;
+          const size_t ti = seq_idx(sq, r0 + i, h, a.H);
           a.dbeta[ti] = sRV[i] - G * d2[r] + ra[r];
           a.dlam[ti] = dlam[r];
         }
@@ -685,7 +691,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gdn_bwd_chunk_kernel(const GdnBwdA
       const float y = __shfl_down(x, off);
       if (l + off < 64) x += y;
     }
-    if (l < nrow) a.dlogalpha[((size_t)b * a.T + r0 + l) * a.H + h] = x;
+    if (l < nrow) a.dlogalpha[seq_idx(sq, r0 + l, h, a.H)] = x;
   }
 }
 

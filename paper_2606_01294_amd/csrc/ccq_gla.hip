@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kThreads, 1) void gla_state_kernel(const GlaStateAr
   const int vt = lb % nvt, kt = (lb / nvt) % nkt, sg = (lb / (nvt * nkt)) % NS, bh = lb / (nvt * nkt * NS);
   const int c0 = kt * BK, v0 = vt * VB;
   const int b = bh / a.H, h = bh % a.H;
-  const Seq sq = seq_of(a.cu, b, a.T);
+  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
   // this segment's chunks (none past a packed sequence's end: the segment then
   // passes its entry state through unchanged, zero sum and unit decay)
   const int cb = sg * SL, ce = min((sq.len + C - 1) / C, cb + SL);
@@ -85,7 +85,8 @@ __global__ __launch_bounds__(kThreads, 1) void gla_state_kernel(const GlaStateAr
   auto prefetch = [&](Stage& st, int ci) {
     const int r0 = ci * C;
     const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
-    st.rk.load(k + seq_off(sq, r0, h, a.H, a.dk) + c0, (size_t)a.H * a.dk, nrow);
+    // (backwards the keys are q_clean, the workspace's rows)
+    st.rk.load(k + seq_off(kRev ? sp : sq, r0, h, a.H, a.dk) + c0, (size_t)a.H * a.dk, nrow);
     if (a.rk) st.fk.load(a.rk + seq_idx(sq, r0, h, a.H), (size_t)a.H, nrow);
     st.rg.load(gate + seq_off(sq, r0, h, a.H, a.dk) + c0, (size_t)a.H * a.dk, nrow);
     st.rv.load(v + seq_off(sq, r0, h, a.H, a.dv) + v0, (size_t)a.H * a.dv, nrow);
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(kOutThreads, 1) void gla_out_kernel(const GlaOutArg
   RowScales<RowTile<T, DK, NT, CARRY>> fk;  // raw keys: row scales (l2 normalisation)
   RowTile<TG, DK, NT, CARRY> rg;
   RowTile<T, VP, NT, CARRY> rv;
-  const Seq sw{(long long)b * a.T, sq.len};  // q_clean: the workspace's padded rows
+  const Seq sw = padded_rows(sq, b, a.T);  // q_clean: the workspace's padded rows
   auto rows = [&](int c) { return (sq.len - c * C) < C ? (sq.len - c * C) : C; };
   auto load_qk = [&](int c) {
     rq.load(static_cast<const T*>(a.qc) + seq_off(sw, c * C, h, a.H, DK), gstride, rows(c));
@@ -671,6 +672,7 @@ hipError_t launch_gla_dstate(const DstateArgs& d, bool is_bf16, bool gate_bf16, 
   a.dk = d.dk;
   a.dv = d.dv;
   a.scale = d.scale;
+  a.cu = d.cu;
   if (is_bf16) return gate_bf16 ? run_gla_state<bf16_t, bf16_t, true>(a, st) : run_gla_state<bf16_t, float, true>(a, st);
   return gate_bf16 ? run_gla_state<float, bf16_t, true>(a, st) : run_gla_state<float, float, true>(a, st);
 }

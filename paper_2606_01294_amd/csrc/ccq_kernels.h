@@ -48,6 +48,7 @@ struct CleanArgs {
   // tensors (length cut at T), or null for a padded [B, T, H, d] batch; the
   // workspace keeps its padded per-chunk layout either way
   const int* cu = nullptr;
+  bool back = false;  // the dq pass: x, base and mdot are workspace rows, the output the caller's
   // raw q, k with per-row l2 normalisation folded in: token t, head h is scaled
   // by rq / rk [rows, H] fp32 (1 / max(|x|, eps)) as it is staged, or null
   const float* rq = nullptr;
@@ -188,6 +189,7 @@ struct DstateArgs {
   void* dstates;      // [B*H, N, dv, dk] io
   int B, T, H, dk, dv;
   float scale;
+  const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
 };
 
 // Chunk-parallel GLA gradients given S_r and dS_{r+1}.
@@ -205,6 +207,7 @@ struct GlaBwdArgs {
   float* dlam;          // [B,T,H]
   int B, T, H, dk, dv;
   float scale;
+  const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
 };
 
 // dg_s = sum_{t >= s} db_t: the chunk's own rows plus dg_next.
@@ -213,6 +216,7 @@ struct DgArgs {
   const float* dg_next;
   void* dg;             // [B,T,H,dk] gate dtype
   int B, T, H, dk;
+  const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
 };
 
 // Key gradient of the contraction (suffix sums of an undecayed dk x dk state,
@@ -232,6 +236,7 @@ struct CcqDkArgs {
   float* hseg;          // [B*H, NS, dk, dk] fp32 workspace: each segment's H
   float* dseg;          // [B*H, NS, dk] fp32 workspace: each segment's D
   float* dchunk;        // [B*H, N, dk] fp32 workspace: each chunk's D
+  const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
 };
 
 // ---- training step (CCQ-Gated DeltaNet backward) ----
@@ -246,6 +251,7 @@ struct GdnPrepArgs {
   void* PT;              // [B*H, N, C, C] io
   void* TmT;             // [B*H, N, C, C] io
   int B, T, H, dk, dv;
+  const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
 };
 
 // Reverse scan of the state adjoint D = dS_{r+1} over the chunks of one head:
@@ -261,6 +267,7 @@ struct GdnDstateArgs {
   void* dR;              // [B,T,H,dv] io
   int B, T, H, dk, dv;
   float scale;
+  const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
 };
 
 // Chunk-parallel Gated DeltaNet gradients given S_r, U, dS_{r+1} and dR.
@@ -281,6 +288,7 @@ struct GdnBwdArgs {
   float* dlam;           // [B,T,H]
   int B, T, H, dk, dv;
   float scale;
+  const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
 };
 
 // ---- recurrent decode (one token per sequence, cache updated in place) ----
@@ -387,13 +395,6 @@ bool decode_supported(int dk, int dv);
 bool decode_split(long long bh, int dk, int dv);  // two launches over 16-row blocks (needs the workspace)
 hipError_t launch_prep(const PrepArgs& a, bool is_bf16, hipStream_t st);
 bool prep_supported(int H, int dk);
-
-// Packed batches: rows of sequence b are cu[b] .. cu[b+1] - 1 of a [rows, ...]
-// tensor whose rows are row_bytes wide (a multiple of 4).  to_padded: packed
-// -> [B, T, ...] with the rows past each sequence's end zeroed; else the
-// sequences' rows back from padded to packed.
-hipError_t launch_varlen_copy(void* dst, const void* src, const int* cu, int B, int T, size_t row_bytes,
-                              bool to_padded, hipStream_t st);
 
 // Supported-shape predicates (used by validation before any launch).
 bool clean_supported(int dk, bool is_bf16);
