@@ -52,6 +52,8 @@ _lock = threading.Lock()
 def lib() -> ctypes.CDLL:
     """Load libccq.so (raises if it has not been built)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -141,13 +143,16 @@ def ccq_workspace_size(shape: Shape, backbone: int, with_bwd: bool = False) -> i
     return int(lib().ccq_workspace_size(ctypes.byref(shape), int(backbone), int(bool(with_bwd))))
 
 
+# The marshalling of a call is the larger part of a decode step of a small batch (its
+# kernel takes 7 us), so it is kept short: pointers and sizes are passed as plain ints
+# (the argument types convert them), the checks of _check run inline on the usual path.
+
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _record(stream, *objs):
@@ -166,7 +171,8 @@ def _record(stream, *objs):
 
 
 def _check(t, name, shape, dtype, device):
-    if t is None:
+    if t is None or (t.shape == shape and t.dtype == dtype and t.device == device and
+                     t.is_contiguous()):
         return
     if tuple(t.shape) != tuple(shape):
         raise ValueError("%s: shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
@@ -481,32 +487,37 @@ def ccq_decode(q, k, v, gate, lam, S, C, mu, t0, backbone=CCQ_GLA, beta=None, sc
     Returns o [B,H,dv]."""
     B, H, dk = q.shape
     dv = v.shape[-1]
-    dev = q.device
-    gate_dtype = gate.dtype if backbone == CCQ_GLA else q.dtype
-    shape = make_shape(B, 1, H, dk, dv, q.dtype, gate_dtype, scale, centered, t0)
-    _check(k, "k", (B, H, dk), q.dtype, dev)
-    _check(v, "v", (B, H, dv), q.dtype, dev)
-    _check(lam, "lam", (B, H), torch.float32, dev)
-    if backbone == CCQ_GLA:
-        _check(gate, "g", (B, H, dk), gate.dtype, dev)
+    dev, dt, f32 = q.device, q.dtype, torch.float32
+    io = _dt(dt)
+    gla = backbone == CCQ_GLA
+    if not gla and beta is None:
+        raise ValueError("beta is required for Gated DeltaNet")
+    if S is None or C is None or mu is None:
+        raise ValueError("%s (the cache) is required" % ("S" if S is None else "C" if C is None else "mu"))
+    key, val, tok = (B, H, dk), (B, H, dv), (B, H)
+    if gla:
+        args = ((gate, "g", key, gate.dtype),)
     else:
-        if beta is None:
-            raise ValueError("beta is required for Gated DeltaNet")
-        _check(gate, "logalpha", (B, H), torch.float32, dev)
-        _check(beta, "beta", (B, H), torch.float32, dev)
-    for t, name, shp in ((S, "S", (B, H, dv, dk)), (C, "C", (B, H, dk, dk)), (mu, "mu", (B, H, dk))):
-        if t is None:
-            raise ValueError("%s (the cache) is required" % name)
-        _check(t, name, shp, torch.float32, dev)
-    o = out if out is not None else torch.empty((B, H, dv), dtype=q.dtype, device=dev)
-    _check(o, "o", (B, H, dv), q.dtype, dev)
-    need = ccq_decode_workspace_size(shape)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    rc = lib().ccq_decode(ctypes.byref(shape), int(backbone), _p(q), _p(k), _p(v), _p(gate),
-                          _p(beta), _p(lam), _p(S), _p(C), _p(mu), _p(o), _p(workspace),
+        args = ((gate, "logalpha", tok, f32), (beta, "beta", tok, f32))
+    for t, name, shp, d in ((k, "k", key, dt), (v, "v", val, dt), (lam, "lam", tok, f32)) + args + (
+            (S, "S", (B, H, dv, dk), f32), (C, "C", (B, H, dk, dk), f32), (mu, "mu", key, f32)):
+        if t is None or t.shape != shp or t.dtype != d or t.device != dev or not t.is_contiguous():
+            _check(t, name, shp, d, dev)
+    o = torch.empty(val, dtype=dt, device=dev) if out is None else out
+    if out is not None:
+        _check(o, "o", val, dt, dev)
+    shape = Shape(B, 1, H, dk, dv, 64, io, _dt(gate.dtype) if gla else io, float(scale),
+                  1 if centered else 0, 0, int(t0))
+    if workspace is None:
+        need = ccq_decode_workspace_size(shape)
+        if need:
+            workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+    rc = lib().ccq_decode(shape, int(backbone), q.data_ptr(), _p(k), v.data_ptr(), gate.data_ptr(),
+                          _p(beta), _p(lam), S.data_ptr(), C.data_ptr(), mu.data_ptr(),
+                          o.data_ptr(), _p(workspace),
                           0 if workspace is None else workspace.numel(), _stream(stream))
-    _record(stream, workspace, o)
+    if stream is not None:
+        _record(stream, workspace, o)
     if rc != 0:
         raise CcqError("ccq_decode", rc)
     return o
