@@ -281,8 +281,7 @@ __global__ __launch_bounds__(G == 1 ? 256 : 64 * G) void clean_prefix_kernel(con
       run_a += sA[u][threadIdx.x & 63];
     }
   }
-#pragma unroll(G == 1 ? 1 : 4)
-  for (int s = sbeg; s < send; ++s) {
+  auto segment = [&](int s) {
     const size_t so = (size_t)bh * NS + s;
     const int cbeg = s * a.seg, cend = min(NCL, cbeg + a.seg);
     float len = (float)(min(sq.len, cend * kChunk) - cbeg * kChunk);
@@ -314,6 +313,12 @@ __global__ __launch_bounds__(G == 1 ? 256 : 64 * G) void clean_prefix_kernel(con
       run_a += tot_a;
       run_b += tot_b;
     }
+  };
+  if constexpr (G == 1) {
+    for (int s = sbeg; s < send; ++s) segment(s);
+  } else {
+#pragma unroll 4
+    for (int s = sbeg; s < send; ++s) segment(s);
   }
   // the final statistics: by the wave whose segments end the sequence (the first
   // one where there are none)

@@ -36,8 +36,11 @@ namespace ccq {
 // chunks from last to first it carries the state adjoint D = dL/dS_{r+1} and
 // stores it for every chunk, with  D^T <- diag(e^{b_C}) D^T + s (Q e^{b})^T dO
 // (a.k = q_clean, a.v = dO, a.states = the adjoints, a.scale = s).
+// (The register bound of two waves per SIMD keeps two workgroups of 128 columns
+// on a compute unit: 42.7 -> 31.5 us at 32 heads of 32 chunks; without it the
+// compiler takes 312 registers.)
 template <typename T, typename TG, int NVT, bool kRev = false>
-__global__ __launch_bounds__(kThreads, 1) void gla_state_kernel(const GlaStateArgs a) {
+__global__ __launch_bounds__(kThreads, NVT >= 8 ? 2 : 1) void gla_state_kernel(const GlaStateArgs a) {
   constexpr int C = kChunk, BK = 64, VB = 16 * NVT;
   constexpr int P = Pad<T>::value, PG = Pad<TG>::value;
   constexpr int LDK = BK + P, LDG = BK + PG, LDV = VB + P;
@@ -201,12 +204,23 @@ __global__ __launch_bounds__(256) void gla_scan_kernel(const GlaScanArgs a) {
   const size_t bh = e4 / DD, el = e4 % DD;
   const int c = (int)(el % a.dk);
   f32x4 x = zero4();
-  for (int j = 0; j < a.NS; ++j) {
-    const size_t so = bh * a.NS + j;
-    if (j > 0) store4(static_cast<T*>(a.entries) + so * DD + el, x[0], x[1], x[2], x[3]);
-    const f32x4 d = *reinterpret_cast<const f32x4*>(a.segdec + so * a.dk + c);
-    const f32x4 s = *reinterpret_cast<const f32x4*>(a.segsum + so * DD + el);
-    x = x * d + s;
+  // (the segments' totals requested four ahead of the chain of products)
+  constexpr int kAhead = 4;
+  for (int j0 = 0; j0 < a.NS; j0 += kAhead) {
+    f32x4 d[kAhead], s[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const size_t so = bh * a.NS + min(j0 + u, a.NS - 1);
+      d[u] = *reinterpret_cast<const f32x4*>(a.segdec + so * a.dk + c);
+      s[u] = *reinterpret_cast<const f32x4*>(a.segsum + so * DD + el);
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int j = j0 + u;
+      if (j >= a.NS) break;
+      if (j > 0) store4(static_cast<T*>(a.entries) + (bh * a.NS + j) * DD + el, x[0], x[1], x[2], x[3]);
+      x = x * d[u] + s[u];
+    }
   }
   if (a.ST) *reinterpret_cast<f32x4*>(a.ST + bh * DD + el) = x;
 }
@@ -578,9 +592,12 @@ hipError_t run_gla_state_v(const GlaStateArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((gla_state_kernel<T, TG, NVT, kRev>), dim3(nblk), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
-// 64-wide value slices when they still give every SIMD a wave, else 32 or 16.
+// 64-wide value slices when they still give every SIMD a wave, else 32 or 16;
+// 128-wide ones where gla_plan cut the sequence for them.
 template <typename T, typename TG, bool kRev = false>
 hipError_t run_gla_state(const GlaStateArgs& a, hipStream_t st) {
+  if constexpr (sizeof(T) == 2 && !kRev)
+    if (a.seg > 0 && a.vs == 128) return run_gla_state_v<T, TG, 8, kRev>(a, st);
   const long long waves64 = (long long)a.B * a.H * (a.dk / 64) * (a.dv / 64) * 4 * gla_nseg(a);
   if (waves64 >= 1024) return run_gla_state_v<T, TG, 4, kRev>(a, st);
   if (waves64 * 2 >= 1024) return run_gla_state_v<T, TG, 2, kRev>(a, st);
