@@ -158,11 +158,8 @@ def kernel_cost(kernel: str, w, io_bytes: int = 2, gate_bytes: int = 2):
         fl = ntok * (2 * dk * dv)
     elif kernel == "gla_bwd_chunk":
         by = ntok * (2 * dk * io_bytes + dk * gate_bytes + 3 * dv * io_bytes + 2 * dv * dk * io_bytes // C
-                     + 4 * dk + 12 * dk + dk * io_bytes + 4)
+                     + 4 * dk + 8 * dk + dk * gate_bytes + dk * io_bytes + 4)
         fl = ntok * (6 * dk * dv + 4 * C * dv + 6 * C * dk)
-    elif kernel == "gla_dg":
-        by = ntok * (4 * dk + dk * gate_bytes)
-        fl = ntok * dk
     elif kernel == "gdn_bwd_prep":  # q_clean, k, gamma, Tm in; decayed scores P^T and Tm^T out
         by = ntok * (2 * dk * io_bytes + 4 + 3 * C * io_bytes)
         fl = ntok * (2 * C * dk)
@@ -282,7 +279,7 @@ KERNELS = {0: ["gla_state"] + CLEAN + ["clean_out", "gla_out"],
            "gla_seg": ["gla_state", "gla_scan"] + CLEAN + ["clean_out", "gla_out"],
            1: ["gdn_tri", "gdn_state"] + CLEAN + ["clean_out", "gdn_out"],
            "train": CLEAN + ["clean_out_train", "gla_state", "gla_out", "gla_dstate",
-                             "gla_bwd_chunk", "gla_dg", "clean_dq", "ccq_dk"],
+                             "gla_bwd_chunk", "clean_dq", "ccq_dk"],
            "gdn_train": CLEAN + ["clean_out_train", "gdn_tri", "gdn_state", "gdn_out",
                                  "gdn_bwd_prep", "gdn_dstate", "gdn_bwd_chunk", "clean_dq",
                                  "ccq_dk"]}
@@ -295,7 +292,7 @@ KERNEL_SYMBOL = {"prep_scales": "prep_kernel (row scales)", "varlen_gather_qk": 
                  "gla_state": "gla_state_kernel", "gla_scan": "gla_scan_kernel", "gla_out": "gla_out_kernel",
                  "gdn_tri": "gdn_tri_kernel", "gdn_state": "gdn_state_dma_kernel",
                  "gdn_out": "gdn_out_kernel", "gla_dstate": "gla_state_kernel (reverse)",
-                 "gla_bwd_chunk": "gla_bwd_chunk_kernel", "gla_dg": "gla_dg_kernel",
+                 "gla_bwd_chunk": "gla_bwd_chunk_kernel",
                  "gdn_bwd_prep": "gdn_bwd_prep_kernel", "gdn_dstate": "gdn_dstate_kernel",
                  "gdn_bwd_chunk": "gdn_bwd_chunk_kernel", "ccq_dk": "ccq_dk_kernel"}
 

@@ -197,7 +197,7 @@ void set_dk_ws(ccq::CcqDkArgs& ka, const ccq_shape* s, char* ws, const DkWs& d) 
 }
 
 struct BwdLayout {
-  size_t qclean, corr, mdq, mdu, states, dstates, dqc, dqc_io, dkg, db, dgn, total;
+  size_t qclean, corr, mdq, mdu, states, dstates, dqc, dqc_io, dkg, total;
   CleanWs clean;
   DkWs dkws;
 };
@@ -218,8 +218,6 @@ BwdLayout bwd_layout(const ccq_shape* s) {
   L.dqc = take(ntok * s->dk * 4);
   L.dqc_io = take(ntok * s->dk * e);
   L.dkg = take(ntok * s->dk * 4);
-  L.db = take(ntok * s->dk * 4);
-  L.dgn = take(nchunk * s->dk * 4);  // dg at each next chunk's first token
   L.clean = take_clean_ws(s, take);
   L.dkws = take_dk_ws(s, take);
   L.total = off;
@@ -513,8 +511,6 @@ ccq_status gla_fwd_bwd(const ccq_shape* s, const int32_t* cu, const void* q, con
   float* mdu = reinterpret_cast<float*>(ws + L.mdu);
   float* dqc = reinterpret_cast<float*>(ws + L.dqc);
   float* dkg = reinterpret_cast<float*>(ws + L.dkg);
-  float* db = reinterpret_cast<float*>(ws + L.db);
-  float* dgn = reinterpret_cast<float*>(ws + L.dgn);
   trace_begin_call();
 
   // forward: cleaned queries (with Sigma q and m.q kept), then GLA keeping S_r
@@ -539,19 +535,16 @@ ccq_status gla_fwd_bwd(const ccq_shape* s, const int32_t* cu, const void* q, con
   // reads only each group's first and carries S through the group
   oa.group = ccq::gla_out_group(s->B, s->H, s->T, s->dk, s->dv, bf);
   if (traced(st, [&] { return ccq::launch_gla_out(oa, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  // backward: dS scan, chunk gradients, decay gradient, dq, dk
+  // backward: dS scan, chunk gradients, dq, dk
   ccq::DstateArgs da{ws + L.qclean, g_or_logalpha, dO, ws + L.dstates, s->B, s->T, s->H, s->dk,
                      s->dv, s->scale};
   da.cu = cu;
   if (traced(st, [&] { return ccq::launch_gla_dstate(da, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   ccq::GlaBwdArgs ba{ws + L.qclean, k, v, g_or_logalpha, dO, ws + L.states, ws + L.dstates, corr,
-                     dqc, ws + L.dqc_io, dkg, dv, db, dgn, dlam, s->B, s->T, s->H, s->dk, s->dv,
+                     dqc, ws + L.dqc_io, dkg, dv, dg_or_dlogalpha, dlam, s->B, s->T, s->H, s->dk, s->dv,
                      s->scale};
   ba.cu = cu;
   if (traced(st, [&] { return ccq::launch_gla_bwd_chunk(ba, bf, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  ccq::DgArgs ga2{db, dgn, dg_or_dlogalpha, s->B, s->T, s->H, s->dk};
-  ga2.cu = cu;
-  if (traced(st, [&] { return ccq::launch_gla_dg(ga2, gbf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   ccq::CleanArgs c2 = clean_args(s, ws, L.clean);  // same keys: statistics reused
   c2.q = ws + L.dqc_io;
   c2.k = k;

@@ -38,8 +38,10 @@
 namespace ccq {
 
 // ----------------------------------------------------------------------------
-// One workgroup per chunk: dqc, the GLA part of dk, dv, the decay gradient
-// db, dlam and the decay gradient at the next chunk's first token, looping
+// One workgroup per chunk: dqc, the GLA part of dk, dv, dlam and the gate
+// gradient dg (the chunk's decay terms db summed in reverse from the decay
+// gradient at the next chunk's first token, so that no sum runs over later
+// chunks), looping
 // over BV-wide slices of the value dimension.  Wave w owns the 16-row stripe
 // w % 4 of the chunk; with eight waves (NW = 8) the two waves of a stripe
 // split its key-channel tiles (and the stripe's dO V^T tiles, the dv tiles
@@ -67,7 +69,8 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
   constexpr int kOffdS = BV * LDQ * ES, kOffV = kOffdS + BV * LDQ * ES,
                 kOffdO = kOffV + C * LDV * ES, kR2 = kOffdO + C * LDV * ES;
   constexpr int kR3 = C * LDT * ES;
-  constexpr int kR4 = (4 + NW) * DK * 4;
+  constexpr int kOffDb = (4 + NW) * DK * 4, kOffPart = kOffDb + C * LDG * 4;
+  constexpr int kR4 = kOffPart + (4 + 1) * DK * 4;
   constexpr int kR = kR2 > kR3 ? kR2 : kR3;
   __shared__ __align__(16) char sR[kR > kR4 ? kR : kR4];
   T* sS = reinterpret_cast<T*>(sR);  // S_r diag(e^{b_m}) slice, rows v
@@ -262,7 +265,8 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
   T* dqc_io = static_cast<T*>(a.dqc_io) + rowoff;
   float* dqc_f = a.dqc + rowoff;
   float* dkg_f = a.dk_gla + rowoff;
-  float* db_f = a.db + rowoff;
+  // the decay terms stay in LDS: the chunk's own reverse sum follows below
+  float* sDb = reinterpret_cast<float*>(sR + kOffDb);
   float qv[NTW][4], kv[NTW][4], cv[NTW][4];
 #pragma unroll
   for (int ct = 0; ct < NTW; ++ct)
@@ -294,7 +298,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
         dqc_f[off] = dqc;
         dqc_io[off] = to<T>(dqc);
         dkg_f[off] = dkg;
-        db_f[off] = db;
+        sDb[i * LDG + c] = db;
         kdk[ct] += kv[ct][r] * inter;
         dl[r] -= dqc * cv[ct][r];
       }
@@ -341,63 +345,40 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
 #pragma unroll
     for (int e = 0; e < 8; ++e) sRow[w * DK + 8 * l + e] = rdot[e];
   lds_barrier();
-  if (tid < DK) {
-    const float kd = sTot[tid] + sTot[DK + tid] + sTot[2 * DK + tid] + sTot[3 * DK + tid];
+  // dg_t = sum_{s >= t} db_s: four threads per channel, 16 rows each, from the
+  // decay gradient at the next chunk's first token.  As a kernel of its own the
+  // sum read back 4 dk bytes a token that this one wrote: 21 us behind this
+  // kernel's 225 us at 16 x 4096 tokens x heads of dk = 128, against 2 us here.
+  constexpr int RPT = C / 4;
+  static_assert(4 * DK == NT, "four threads per channel");
+  float* sPart = reinterpret_cast<float*>(sR + kOffPart);  // [4][DK], then the next chunk's [DK]
+  const int ch = tid % DK, part = tid / DK;
+  float x[RPT], run = 0.f;
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    const int row = RPT * part + j;
+    x[j] = row < nrow ? sDb[row * LDG + ch] : 0.f;
+    run += x[j];
+  }
+  sPart[part * DK + ch] = run;
+  if (part == 0) {
+    const float kd = sTot[ch] + sTot[DK + ch] + sTot[2 * DK + ch] + sTot[3 * DK + ch];
     float sd = 0.f;
 #pragma unroll
-    for (int ww = 0; ww < NW; ++ww) sd += sRow[ww * DK + tid];
-    a.dg_next[((size_t)bh * N + ci) * DK + tid] = __expf(sG[(C - 1) * LDG + tid]) * sd + kd;
+    for (int ww = 0; ww < NW; ++ww) sd += sRow[ww * DK + ch];
+    sPart[4 * DK + ch] = __expf(sG[(C - 1) * LDG + ch]) * sd + kd;
   }
-}
-
-// ----------------------------------------------------------------------------
-// dg_t = sum_{s >= t} db_s: one workgroup per chunk, one thread per channel;
-// the rows of the chunk are summed here and the later chunks enter through the
-// decay gradient at the next chunk's first token (dg_next).
-template <typename TG>
-__global__ __launch_bounds__(kThreads) void gla_dg_kernel(const DgArgs a) {
-  constexpr int C = kChunk, HC = C / 2;
-  __shared__ float sHalf[kThreads];
-  const int N = (a.T + C - 1) / C;
-  const int lb = blockIdx.x;
-  const int bh = lb / N, ci = lb % N;
-  const int b = bh / a.H, h = bh % a.H;
-  const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
-  const int r0 = ci * C;
-  if (r0 >= sq.len) return;  // past a packed sequence's end
-  const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
-  const int hd = a.H * a.dk;
-  TG* dg = static_cast<TG*>(a.dg) + seq_off(sq, r0, h, a.H, a.dk);
-  const float* db = a.db + seq_off(sp, r0, h, a.H, a.dk);
-  // thread (c, half): half 1 takes rows 32..63 of channel c, half 0 rows 0..31
-  const int npc = kThreads / 2;  // channels per pass
-  for (int c0 = 0; c0 < a.dk; c0 += npc) {
-    const int c = c0 + (threadIdx.x % npc), half = threadIdx.x / npc;
-    const bool on = c < a.dk;
-    // sum over the later chunks (half 1 only)
-    const float later = (on && half == 1) ? a.dg_next[((size_t)bh * N + ci) * a.dk + c] : 0.f;
-    float x[HC];
+  lds_barrier();
+  float acc = sPart[4 * DK + ch];
 #pragma unroll
-    for (int j = 0; j < HC; ++j) {
-      const int row = HC * half + j;
-      x[j] = on ? db[(row < nrow ? row : nrow - 1) * hd + c] : 0.f;
-    }
-    float run = 0.f;  // sum of this half's rows
+  for (int p = 3; p > 0; --p)
+    if (p > part) acc += sPart[p * DK + ch];
+  TG* dg = static_cast<TG*>(a.dg) + seq_off(sq, r0, h, a.H, DK) + ch;
 #pragma unroll
-    for (int j = 0; j < HC; ++j) run += (HC * half + j < nrow) ? x[j] : 0.f;
-    sHalf[threadIdx.x] = run + later;
-    __syncthreads();
-    // half 0 starts from everything after row 31; half 1 from the later chunks
-    float acc = half == 0 ? sHalf[threadIdx.x + npc] : later;
-    __syncthreads();
-#pragma unroll
-    for (int j = HC - 1; j >= 0; --j) {
-      const int row = HC * half + j;
-      if (on && row < nrow) {
-        acc += x[j];
-        dg[row * hd + c] = static_cast<TG>(acc);
-      }
-    }
+  for (int j = RPT - 1; j >= 0; --j) {
+    const int row = RPT * part + j;
+    acc += x[j];
+    if (row < nrow) dg[row * (int)gsk] = static_cast<TG>(acc);
   }
 }
 
@@ -899,16 +880,6 @@ bool bwd_supported(int dk, int dv, bool is_bf16, bool gdn) {
 hipError_t launch_gla_bwd_chunk(const GlaBwdArgs& a, bool is_bf16, bool gate_bf16, hipStream_t st) {
   if (is_bf16) return gate_bf16 ? chunk_dispatch<bf16_t, bf16_t>(a, st) : chunk_dispatch<bf16_t, float>(a, st);
   return gate_bf16 ? chunk_dispatch<float, bf16_t>(a, st) : chunk_dispatch<float, float>(a, st);
-}
-
-hipError_t launch_gla_dg(const DgArgs& a, bool gate_bf16, hipStream_t st) {
-  const int nblk = a.B * a.H * ((a.T + kChunk - 1) / kChunk);
-  if (nblk == 0) return hipSuccess;
-  if (gate_bf16)
-    hipLaunchKernelGGL(gla_dg_kernel<bf16_t>, dim3(nblk), dim3(kThreads), 0, st, a);
-  else
-    hipLaunchKernelGGL(gla_dg_kernel<float>, dim3(nblk), dim3(kThreads), 0, st, a);
-  return hipGetLastError();
 }
 
 hipError_t launch_ccq_dk(const CcqDkArgs& a, bool is_bf16, hipStream_t st) {

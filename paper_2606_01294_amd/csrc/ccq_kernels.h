@@ -203,20 +203,10 @@ struct GlaBwdArgs {
   void* dqc_io;         // same, io dtype
   float* dk_gla;        // GLA part of dL/dk [B,T,H,dk] fp32
   void* dv_out;         // [B,T,H,dv] io
-  float* db;            // dL/d(cumulative log decay) [B,T,H,dk] fp32
-  float* dg_next;       // decay gradient at the first token of the next chunk [B*H, N, dk]
+  void* dg;             // [B,T,H,dk] gate dtype
   float* dlam;          // [B,T,H]
   int B, T, H, dk, dv;
   float scale;
-  const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
-};
-
-// dg_s = sum_{t >= s} db_t: the chunk's own rows plus dg_next.
-struct DgArgs {
-  const float* db;
-  const float* dg_next;
-  void* dg;             // [B,T,H,dk] gate dtype
-  int B, T, H, dk;
   const int* cu = nullptr;  // packed-batch offsets (device), as CleanArgs
 };
 
@@ -399,7 +389,6 @@ hipError_t launch_copy_or_zero(float* dst, const float* src, size_t n, hipStream
 
 hipError_t launch_gla_dstate(const DstateArgs& a, bool is_bf16, bool gate_bf16, hipStream_t st);
 hipError_t launch_gla_bwd_chunk(const GlaBwdArgs& a, bool is_bf16, bool gate_bf16, hipStream_t st);
-hipError_t launch_gla_dg(const DgArgs& a, bool gate_bf16, hipStream_t st);
 hipError_t launch_ccq_dk(const CcqDkArgs& a, bool is_bf16, hipStream_t st);
 // Training-step shapes: bf16 dk in {64, 128} (and 256 for Gated DeltaNet), fp32 dk = 64.
 bool bwd_supported(int dk, int dv, bool is_bf16, bool gdn);
