@@ -763,9 +763,11 @@ hipError_t launch_gdn_bwd_chunk(const GdnBwdArgs& a, bool is_bf16, hipStream_t s
   if (is_bf16) {
     switch (a.dk) {
       case 64: return run_bwd_chunk<bf16_t, 64>(a, st);
-      case 128: return run_bwd_chunk<bf16_t, 128>(a, st);
-      // eight waves at dk = 256 (the kernel takes a compute unit's LDS: two
-      // waves per SIMD instead of one)
+      // eight waves from dk = 128 on: the LDS admits one workgroup a compute
+      // unit, so four waves leave each SIMD with one (and with 398 registers,
+      // 142 of them reached through moves).  dk = 128, 8 packed sequences of up
+      // to 2048 tokens x 4 heads, dv = 256: 137 us with four waves, 109 with eight
+      case 128: return run_bwd_chunk<bf16_t, 128, 8>(a, st);
       case 256: return run_bwd_chunk<bf16_t, 256, 8>(a, st);
     }
   } else if (a.dk == 64) {
