@@ -388,31 +388,39 @@ __global__ __launch_bounds__(64 * NW, 1) void gla_bwd_chunk_kernel(const GlaBwdA
 //   H_j = sum_{t > chunk of j} rho_t (u_t q_t^T + q_t u_t^T),  rho_t = -lam_t / t,
 //   D_j = sum_{t > chunk of j} (lam_t/t^2) (u_t (m_t.q_t) + q_t (m_t.u_t)).
 // Both are plain (undecayed) sums, so the chunks are cut into segments of
-// `seg`: ccq_dk_stats_kernel forms every segment's H and D and every chunk's
-// D (one workgroup per segment, all segments in parallel), and
-// ccq_dk_kernel starts each segment from the sum over the later segments and
-// walks the segment's chunks from last to first.  For large DK the 16 x 16
-// tiles of H (and the output columns of ccq_dk_kernel) are split over NSPLIT
-// workgroups per segment; each stages the whole chunk.
+// `seg`: ccq_dk_stats_kernel forms every segment's D, every chunk's D and the
+// segment's X = sum_t rho_t u_t q_t^T (one workgroup per segment, all segments
+// in parallel), and ccq_dk_kernel starts each segment from H = X + X^T of the
+// sum over the later segments and walks the segment's chunks from last to
+// first.  For large DK the 16 x 16 tiles of X (and the output columns of
+// ccq_dk_kernel) are split over NSPLIT workgroups per segment; each stages the
+// whole chunk.
+// The statistics are bound by their LDS reads: X takes half of H's products,
+// and a wave's BT x BT block of its tiles a quarter of the reads of a row of
+// them.  4 x 4096 tokens x 8 heads, DK = 256: 123 us with H's tiles by rows, 60
+// with X in blocks; DK = 128: 33 and 26 us.
 // Both kernels stage q and rho u as row-major chunk tiles (16-byte writes) and
 // read them feature-major with transposing reads where a product runs over the
 // chunk's rows.
 template <typename T, int DK, int NSPLIT, int NWV>
-__global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_stats_kernel(const CcqDkArgs a) {
+__global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void ccq_dk_stats_kernel(const CcqDkArgs a) {
   constexpr int C = kChunk;
   constexpr int P = Pad<T>::value;
   constexpr int LDQ = DK + P;
   constexpr int NTHR = 64 * NWV;
   constexpr int NT16 = DK / 16, NPW = NT16 * NT16 / (NWV * NSPLIT);
-  constexpr int NPART = NTHR / DK;
-  static_assert(NPW >= 1 && NTHR % DK == 0, "tile split");
+  constexpr int BT = NPW == 16 ? 4 : 2;  // a wave's tiles of X: a BT x BT block
+  static_assert(BT * BT == NPW && NT16 % BT == 0, "tile split");
+  // the mean-term vector: NCH of the channels per workgroup, a thread taking two
+  constexpr int NCH = DK / NSPLIT, NPART = NTHR / (NCH / 2);
+  static_assert(NTHR % (NCH / 2) == 0 && C % NPART == 0, "mean-term split");
   // row-major staging with coalesced loads (adjacent lanes along a row)
   typedef RowTile<T, DK, NTHR> Tile;
 
   __shared__ __align__(16) T sQ[C * LDQ];
   __shared__ __align__(16) T sRU[C * LDQ];  // rho u
-  __shared__ float sA[C], sB[C];            // -(m.q)/t and -rho (m.u)/t
-  __shared__ float sDp[NTHR];
+  __shared__ float2 sAB[C];                 // -(m.q)/t and -rho (m.u)/t
+  __shared__ float2 sDp[NTHR];
 
   const int N = (a.T + C - 1) / C;
   const int NS = (N + a.seg - 1) / a.seg;
@@ -425,7 +433,8 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_stats_kernel(const CcqDkAr
   const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
   const int tid = threadIdx.x, w = wave_id(), l = lane_id();
   const int g4 = l >> 4, c16 = l & 15;
-  const int tw0 = (split * NWV + w) * NPW;  // first tile of this wave
+  const int blk = split * NWV + w;  // this wave's block of X
+  const int br = blk / (NT16 / BT) * BT, bc = blk % (NT16 / BT) * BT;
   const T* q = static_cast<const T*>(a.q);
   const T* uu = static_cast<const T*>(a.u);
   const size_t gs = (size_t)a.H * DK;
@@ -434,9 +443,11 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_stats_kernel(const CcqDkAr
   const int NL = (sq.len + C - 1) / C;
   const int c_end = (c_begin + a.seg) < NL ? (c_begin + a.seg) : NL;
 
-  f32x4 H[NPW];
+  f32x4 X[BT][BT];
 #pragma unroll
-  for (int u = 0; u < NPW; ++u) H[u] = zero4();
+  for (int x = 0; x < BT; ++x)
+#pragma unroll
+    for (int y = 0; y < BT; ++y) X[x][y] = zero4();
   float dsum = 0.f;
 
   Tile rq, ru;
@@ -463,8 +474,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_stats_kernel(const CcqDkAr
       if (w == 0) {
         const float tpos = (float)(ci * C + l + 1);
         const float rho = -rlam.get() / tpos;
-        sA[l] = a.centered ? -rmq.get() / tpos : 0.f;
-        sB[l] = a.centered ? -rho * rmu.get() / tpos : 0.f;
+        sAB[l] = a.centered ? make_float2(-rmq.get() / tpos, -rho * rmu.get() / tpos) : make_float2(0.f, 0.f);
       }
       rq.store(sQ, LDQ);
 #pragma unroll
@@ -482,44 +492,59 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_stats_kernel(const CcqDkAr
     if (ci + 1 < c_end) prefetch(ci + 1);
     lds_barrier();
 #pragma unroll
-    for (int u = 0; u < NPW; ++u) {
-      const int tau = tw0 + u, tr = tau / NT16, tc = tau % NT16;
-      tile_mma_tr<T, C>(H[u], sRU + 16 * tr, LDQ, sQ + 16 * tc, LDQ);
-      tile_mma_tr<T, C>(H[u], sQ + 16 * tr, LDQ, sRU + 16 * tc, LDQ);
+    for (int m = 0; m < C / 32; ++m) {
+      Frag<T> fu[BT], fq[BT];
+#pragma unroll
+      for (int x = 0; x < BT; ++x) {
+        fu[x] = ld_frag_tr(sRU + 32 * m * LDQ + 16 * (br + x), LDQ);
+        fq[x] = ld_frag_tr(sQ + 32 * m * LDQ + 16 * (bc + x), LDQ);
+      }
+#pragma unroll
+      for (int x = 0; x < BT; ++x)
+#pragma unroll
+        for (int y = 0; y < BT; ++y) mma(X[x][y], fu[x], fq[y]);
     }
-    if (split == 0) {  // this chunk's mean-term vector, NPART threads per key channel
-      const int n = tid % DK, part = tid / DK;
-      float x = 0.f;
-#pragma unroll 8
-      for (int t = part * (C / NPART); t < (part + 1) * (C / NPART); ++t)
-        x += sA[t] * f32(sRU[t * LDQ + n]) + sB[t] * f32(sQ[t * LDQ + n]);
+    {  // this chunk's mean-term vector, NPART threads per two key channels
+      typedef T pair_t __attribute__((ext_vector_type(2)));
+      const int n = split * NCH + 2 * (tid % (NCH / 2)), part = tid / (NCH / 2);
+      float2 x = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int t = part * (C / NPART); t < (part + 1) * (C / NPART); ++t) {
+        const float2 ab = sAB[t];
+        const pair_t ru2 = *reinterpret_cast<const pair_t*>(sRU + t * LDQ + n);
+        const pair_t q2 = *reinterpret_cast<const pair_t*>(sQ + t * LDQ + n);
+        x.x += ab.x * f32(ru2[0]) + ab.y * f32(q2[0]);
+        x.y += ab.x * f32(ru2[1]) + ab.y * f32(q2[1]);
+      }
       sDp[tid] = x;
     }
     lds_barrier();
-    if (split == 0 && tid < DK) {
-      float x = sDp[tid];
+    if (tid < NCH) {
+      const float* dp = reinterpret_cast<const float*>(sDp) + tid;
+      float x = dp[0];
 #pragma unroll
-      for (int p2 = 1; p2 < NPART; ++p2) x += sDp[p2 * DK + tid];
-      a.dchunk[((size_t)bh * N + ci) * DK + tid] = x;
+      for (int p2 = 1; p2 < NPART; ++p2) x += dp[p2 * NCH];
+      a.dchunk[((size_t)bh * N + ci) * DK + split * NCH + tid] = x;
       dsum += x;
     }
   }
   float* hs = a.hseg + ((size_t)bh * NS + sg) * DK * DK;
 #pragma unroll
-  for (int u = 0; u < NPW; ++u) {
-    const int tau = tw0 + u, tr = tau / NT16, tc = tau % NT16;
+  for (int x = 0; x < BT; ++x)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) hs[(size_t)(16 * tr + 4 * g4 + r) * DK + 16 * tc + c16] = H[u][r];
-  }
-  if (split == 0 && tid < DK) a.dseg[((size_t)bh * NS + sg) * DK + tid] = dsum;
+    for (int y = 0; y < BT; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        hs[(size_t)(16 * (br + x) + 4 * g4 + r) * DK + 16 * (bc + y) + c16] = X[x][y][r];
+  if (tid < NCH) a.dseg[((size_t)bh * NS + sg) * DK + split * NCH + tid] = dsum;
 }
 
-// In place, per head: segment s's H and D become the sums over the later
+// In place, per head: segment s's X and D become the sums over the later
 // segments s' > s (exclusive suffix sums), four elements per thread.
 __global__ __launch_bounds__(kThreads) void ccq_dk_suffix_kernel(const CcqDkArgs a) {
   const int N = (a.T + kChunk - 1) / kChunk;
   const int NS = (N + a.seg - 1) / a.seg;
-  const size_t per = (size_t)a.dk * a.dk + a.dk;  // H and D elements of one segment
+  const size_t per = (size_t)a.dk * a.dk + a.dk;  // X and D elements of one segment
   const size_t i4 = ((size_t)blockIdx.x * kThreads + threadIdx.x) * 4;
   const int bh = blockIdx.y;
   if (i4 >= per) return;
@@ -579,7 +604,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
   const int bh = lb / NS, sg = lb % NS;
   const int b = bh / a.H, h = bh % a.H;
   const Seq sq = seq_of(a.cu, b, a.T), sp = padded_rows(sq, b, a.T);
-  const int tid = threadIdx.x, w = wave_id(), l = lane_id();
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id()), l = lane_id();
   const int g4 = l >> 4, c16 = l & 15;
   const int nt0 = (split * NWV + w) * NTW;  // first output column tile of this wave
   const T* q = static_cast<const T*>(a.q);
@@ -611,7 +636,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) Hc[ct][x] = zero4();
   }
-  {  // H[c][n] = H[n][c] (H is symmetric): four consecutive c per load
+  {  // H[c][n] = X[n][c] + X[c][n]
     const float* hs = a.hseg + ((size_t)bh * NS + sg) * DK * DK;
 #pragma unroll
     for (int x = 0; x < NTW; ++x) {
@@ -620,25 +645,37 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct)
         Hc[ct][x] = *reinterpret_cast<const f32x4*>(hs + (size_t)n * DK + 16 * ct + 4 * g4);
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Hc[ct][x][r] += hs[(size_t)(16 * ct + 4 * g4 + r) * DK + n];
     }
   }
 
   Tile rq, ru, rk;
   RowScales<Tile> fl;         // lambda of each staged vector's row
   RowScalar rlam, rmq, rmu;   // wave 0: lane = row
+  // At DK = 256 the row offsets are formed at the loads, and u and k are
+  // requested only once dk's rows are formed (H's update covers them): the
+  // products over H then fit the registers.  Any spill is reloaded behind the
+  // requests of the next chunk and so waits for them: 31 spilled registers cost
+  // 80 of 272 us at 4 x 4096 tokens x 8 heads.
+  constexpr bool kLate = DK >= 256;
+  auto ld = [&](Tile& t, const T* src, int nrow) {
+    if constexpr (kLate) t.load_opaque(src, gs, nrow);
+    else t.load(src, gs, nrow);
+  };
+  auto prefetch_uk = [&](int ci) {
+    const int r0 = ci * C;
+    const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
+    ld(ru, uu + seq_off(sp, r0, h, a.H, DK), nrow);
+    ld(rk, k + seq_off(sq, r0, h, a.H, DK), nrow);
+  };
   auto prefetch = [&](int ci) {
     const int r0 = ci * C;
     const int nrow = (sq.len - r0) < C ? (sq.len - r0) : C;
-    // (at DK = 256 with the row offsets formed at the loads: fewer registers
-    // held across the chunk loop, less spill; measured 437 -> 426 us there,
-    // slightly slower at DK = 128)
-    auto ld = [&](Tile& t, const T* src) {
-      if constexpr (DK >= 256) t.load_opaque(src, gs, nrow);
-      else t.load(src, gs, nrow);
-    };
-    ld(rq, q + seq_off(sq, r0, h, a.H, DK));
-    ld(ru, uu + seq_off(sp, r0, h, a.H, DK));
-    ld(rk, k + seq_off(sq, r0, h, a.H, DK));
+    ld(rq, q + seq_off(sq, r0, h, a.H, DK), nrow);
+    if constexpr (!kLate) prefetch_uk(ci);
     const size_t ti = seq_idx(sq, r0, h, a.H), tp = seq_idx(sp, r0, h, a.H);
     fl.load(a.lam + ti, (size_t)a.H, nrow);
     if (w == 0) {
@@ -647,7 +684,10 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
       rmu.load(a.mdot_u + tp, (size_t)a.H, l, nrow);
     }
   };
-  if (c_begin < c_end) prefetch(c_end - 1);
+  if (c_begin < c_end) {
+    prefetch(c_end - 1);
+    if constexpr (kLate) prefetch_uk(c_end - 1);
+  }
 
   for (int ci = c_end - 1; ci >= c_begin; --ci) {
     const int r0 = ci * C;
@@ -699,9 +739,11 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
     lds_barrier();  // (B)
 
     // intra weights: the ten tiles on or below the diagonal, over the waves
+    int wi = w;  // opaque: the tiles' addresses are formed here, not held across the loop
+    asm volatile("" : "+s"(wi));
 #pragma unroll
     for (int s3 = 0; s3 < (10 + NWV - 1) / NWV; ++s3) {
-      const int t = w + NWV * s3;
+      const int t = wi + NWV * s3;
       if (t < 10) {
         const int I = intra_tile_row(t), J = intra_tile_col(t);
         f32x4 s1 = zero4(), s2 = zero4();  // q . k and (rho u) . k
@@ -711,24 +753,32 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
           mma(s1, ld_frag(sQ + 16 * I * LDQ + k0, LDQ), kf);
           mma(s2, ld_frag(sRU + 16 * I * LDQ + k0, LDQ), kf);
         }
+        const int jj = 16 * J + c16, wo = jj * LDA + 16 * I + 4 * g4;
+        float w1[4], w2[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int tt = 16 * I + 4 * g4 + r, jj = 16 * J + c16;
+          const int tt = 16 * I + 4 * g4 + r;
           const bool on = jj <= tt;
-          const float w1 = on ? s1[r] - sMq[tt] : 0.f;
-          const float w2 = on ? s2[r] - sRho[tt] * sMu[tt] : 0.f;
-          if constexpr (kSplit) {
+          w1[r] = on ? s1[r] - sMq[tt] : 0.f;
+          w2[r] = on ? s2[r] - sRho[tt] * sMu[tt] : 0.f;
+        }
+        if constexpr (kSplit) {
+          bf16x4 h1, l1, h2, l2;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
             bf16_t hi, lo;
-            split_bf16(w1, hi, lo);
-            sW1h[jj * LDA + tt] = hi;
-            sW1l[jj * LDA + tt] = lo;
-            split_bf16(w2, hi, lo);
-            sW2h[jj * LDA + tt] = hi;
-            sW2l[jj * LDA + tt] = lo;
-          } else {
-            sW1h[jj * LDA + tt] = w1;
-            sW2h[jj * LDA + tt] = w2;
+            split_bf16(w1[r], hi, lo);
+            h1[r] = hi, l1[r] = lo;
+            split_bf16(w2[r], hi, lo);
+            h2[r] = hi, l2[r] = lo;
           }
+          *reinterpret_cast<bf16x4*>(sW1h + wo) = h1;
+          *reinterpret_cast<bf16x4*>(sW1l + wo) = l1;
+          *reinterpret_cast<bf16x4*>(sW2h + wo) = h2;
+          *reinterpret_cast<bf16x4*>(sW2l + wo) = l2;
+        } else {
+          store4(sW1h + wo, w1[0], w1[1], w1[2], w1[3]);
+          store4(sW2h + wo, w2[0], w2[1], w2[2], w2[3]);
         }
       }
     }
@@ -778,6 +828,7 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
       for (int J = 0; J < 4; ++J) {
 #pragma unroll
         for (int m2 = 0; m2 < 2; ++m2) {
+          if (32 * m2 + 31 < 16 * J) continue;  // t < j
           mma(acc[J], ld_frag(sW1h + 16 * J * LDA + 32 * m2, LDA), f1[m2]);
           mma(acc[J], ld_frag(sW2h + 16 * J * LDA + 32 * m2, LDA), f2[m2]);
           if constexpr (kSplit) {
@@ -795,6 +846,8 @@ __global__ __launch_bounds__(64 * NWV, 1) void ccq_dk_kernel(const CcqDkArgs a) 
       }
     }
 
+    if (ci == c_begin) break;  // no earlier chunk takes this one's terms
+    if constexpr (kLate) prefetch_uk(ci - 1);
     // H += (rho u)^T q + q^T (rho u) for this wave's columns; D += this chunk's D
     Frag<T> bq[NTW][2], bu[NTW][2];
 #pragma unroll
