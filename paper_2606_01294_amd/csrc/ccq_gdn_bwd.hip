@@ -105,17 +105,24 @@ __global__ __launch_bounds__(kThreads) void gdn_bwd_prep_kernel(const GdnPrepArg
 // owns NPR value tiles of 16, each split over NH waves by key feature: wave
 // (p, hq) keeps D^T[c][v] for its DK / NH features c of tile p in MFMA
 // accumulators.  Per chunk (last to first):
-//   store D;  X = diag(e^{gamma_C - gamma}) K D^T (partial over each wave's
-//   features, summed over the NH waves through LDS in a fixed order);
-//   dU = X + PT dO';  dR = Tm^T dU -> stored;
+//   store D;  dU = diag(e^{gamma_C - gamma}) K D^T + PT dO' (partial: each
+//   wave's features, and PT's rows shared out over the NH waves; summed over
+//   them through LDS in a fixed order);  dR = Tm^T dU -> stored;
 //   D <- e^{gamma_C} D + (G Q)^T dO' - K^T diag(beta G) dR.
 // The chunk's K, G Q, PT, Tm^T and dO' slice are prefetched into registers
 // one chunk ahead and staged through LDS; K and q (the bulk of it) are
 // requested after the partial-sum exchange and D is stored there too, so that
 // the issue of those loads and stores overlaps the chunk's products (measured
 // at the 1.3B training shape: 471 -> 406 us).
+// The chain over the chunks is bound by its LDS round trips and barriers: at
+// dk = 256 a form that summed one row tile of dU per wave read a third of the
+// exchange but took two more barriers, 319 -> 328 us.  Four waves with two
+// feature halves keep to 256 registers (no moves through the accumulation
+// registers): 114 -> 110 us on 8 packed sequences of up to 2048 tokens x 4
+// heads, dk = 128, dv = 256, PT's share included.
 template <typename T, int DK, int NPR, int NH>
-__global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnDstateArgs a) {
+__global__ __launch_bounds__(64 * NPR * NH, (NPR * NH == 4 && NH == 2 && sizeof(T) == 2 && DK <= 128) ? 2 : 1)
+void gdn_dstate_kernel(const GdnDstateArgs a) {
   constexpr int C = kChunk, NW = NPR * NH, NT = 64 * NW, BVS = 16 * NPR;
   constexpr int P = Pad<T>::value;
   constexpr int LDQ = DK + P, LDP = C + P;
@@ -129,7 +136,7 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnD
   __shared__ __align__(16) T sTT[C * LDP];     // Tm^T, rows in acc_pos order
   __shared__ __align__(16) T sdOT[BVS * LDP];  // (s dO)^T of the workgroup's values
   __shared__ __align__(16) float sCf[3][C];    // e^{gamma_C - gamma}, beta e^gamma, e^{gamma_C}
-  __shared__ __align__(16) f32x4 sX[NH > 1 ? NW * 4 * 64 : 1];  // partial X of every wave
+  __shared__ __align__(16) f32x4 sX[NH > 1 ? NW * 4 * 64 : 1];  // partial dU of every wave
 
   const int nvt = a.dv / BVS;
   const int N = (a.T + C - 1) / C;
@@ -257,12 +264,46 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnD
       for (int m = 0; m < NK; ++m)
         mma(dU[I], ld_frag_acc(sK + 16 * I * LDQ + c0 + 32 * m, (size_t)LDQ), df[m]);
     }
+    const Frag<T> of0 = ld_frag(sdOT + 16 * pr * LDP, LDP);
+    const Frag<T> of1 = ld_frag(sdOT + 16 * pr * LDP + 32, LDP);
+    // the rows' scale, and PT dO' for the wave's 4 / NH row tiles
+#pragma unroll
+    for (int I = 0; I < 4; ++I) {
+      dU[I] *= *reinterpret_cast<const f32x4*>(&sCf[0][16 * I + 4 * g4]);
+      if (I * NH / 4 == hq) {
+        mma(dU[I], ld_frag(sPT + 16 * I * LDP, LDP), of0);
+        mma(dU[I], ld_frag(sPT + 16 * I * LDP + 32, LDP), of1);
+      }
+    }
     if constexpr (NH > 1) {
-      // sum the NH partial products of this value tile, in a fixed order so
-      // every wave of the tile holds bit-identical X
 #pragma unroll
       for (int I = 0; I < 4; ++I) sX[(w * 4 + I) * 64 + l] = dU[I];
       lds_barrier();
+    }
+    T* dRrow = dRg + seq_off(sp, r0, h, a.H, a.dv) + v;
+    auto store_dR = [&](int I, const f32x4& x) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * I + 4 * g4 + r;
+        if (i < nrow) dRrow[i * a.H * a.dv] = to<T>(x[r]);
+      }
+    };
+    // D is the adjoint of the state leaving chunk ci (stored here, after the
+    // exchange, so that its issue overlaps the products too)
+    auto store_D = [&] {
+      T* out = dst + (cidx * a.dv + v) * DK + c0 + 4 * g4;
+#pragma unroll
+      for (int tc = 0; tc < NCT; ++tc) store4(out + 16 * tc, D[tc][0], D[tc][1], D[tc][2], D[tc][3]);
+    };
+    const float eC = sCf[2][0];
+    auto add_q = [&](int tc) {  // D <- e^{gamma_C} D + (G Q)^T dO'
+      D[tc] *= eC;
+      mma(D[tc], ld_frag_tr(sQ + c0 + 16 * tc, LDQ), of0);
+      mma(D[tc], ld_frag_tr(sQ + 32 * LDQ + c0 + 16 * tc, LDQ), of1);
+    };
+    if constexpr (NH > 1)
+      // the NH partial products in a fixed order, so that every wave of the
+      // tile holds bit-identical dU
 #pragma unroll
       for (int I = 0; I < 4; ++I) {
         f32x4 sum = sX[((pr * NH) * 4 + I) * 64 + l];
@@ -270,25 +311,8 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnD
         for (int hh = 1; hh < NH; ++hh) sum += sX[((pr * NH + hh) * 4 + I) * 64 + l];
         dU[I] = sum;
       }
-    }
     if (ci > 0) prefetch_kq(ci - 1);
-    {  // D is the adjoint of the state leaving chunk ci (stored here, after the
-       // exchange, so that its issue overlaps the products too)
-      T* out = dst + (cidx * a.dv + v) * DK + c0 + 4 * g4;
-#pragma unroll
-      for (int tc = 0; tc < NCT; ++tc) store4(out + 16 * tc, D[tc][0], D[tc][1], D[tc][2], D[tc][3]);
-    }
-#pragma unroll
-    for (int I = 0; I < 4; ++I) dU[I] *= *reinterpret_cast<const f32x4*>(&sCf[0][16 * I + 4 * g4]);
-    // dU += PT dO'
-    const Frag<T> of0 = ld_frag(sdOT + 16 * pr * LDP, LDP);
-    const Frag<T> of1 = ld_frag(sdOT + 16 * pr * LDP + 32, LDP);
-#pragma unroll
-    for (int I = 0; I < 4; ++I) {
-      mma(dU[I], ld_frag(sPT + 16 * I * LDP, LDP), of0);
-      mma(dU[I], ld_frag(sPT + 16 * I * LDP + 32, LDP), of1);
-    }
-    T* dRrow = dRg + seq_off(sp, r0, h, a.H, a.dv) + v;
+    store_D();
     // dR = Tm^T dU
     const Frag<T> uf0 = acc_pair_frag<T>(dU[0], dU[1]);
     const Frag<T> uf1 = acc_pair_frag<T>(dU[2], dU[3]);
@@ -299,25 +323,18 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_dstate_kernel(const GdnD
       mma(dR[I], ld_frag(sTT + 16 * I * LDP, LDP), uf0);
       mma(dR[I], ld_frag(sTT + 16 * I * LDP + 32, LDP), uf1);
     }
-    if (hq == 0)
 #pragma unroll
-      for (int I = 0; I < 4; ++I)
+    for (int I = 0; I < 4; ++I) {
+      if (I * NH / 4 == hq) store_dR(I, dR[I]);
+      dR[I] *= -*reinterpret_cast<const f32x4*>(&sCf[1][16 * I + 4 * g4]);
+    }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 16 * I + 4 * g4 + r;
-          if (i < nrow) dRrow[i * a.H * a.dv] = to<T>(dR[I][r]);
-        }
-    // D <- e^{gamma_C} D + (G Q)^T dO' - K^T diag(beta G) dR
-#pragma unroll
-    for (int I = 0; I < 4; ++I) dR[I] *= -*reinterpret_cast<const f32x4*>(&sCf[1][16 * I + 4 * g4]);
+    for (int tc = 0; tc < NCT; ++tc) add_q(tc);
     const Frag<T> rf0 = acc_pair_frag<T>(dR[0], dR[1]);
     const Frag<T> rf1 = acc_pair_frag<T>(dR[2], dR[3]);
-    const float eC = sCf[2][0];
+    // D <- D - K^T diag(beta G) dR
 #pragma unroll
     for (int tc = 0; tc < NCT; ++tc) {
-      D[tc] *= eC;
-      mma(D[tc], ld_frag_tr(sQ + c0 + 16 * tc, LDQ), of0);
-      mma(D[tc], ld_frag_tr(sQ + 32 * LDQ + c0 + 16 * tc, LDQ), of1);
       mma(D[tc], ld_frag_tr_acc(sK + c0 + 16 * tc, LDQ), rf0);
       mma(D[tc], ld_frag_tr_acc(sK + 32 * LDQ + c0 + 16 * tc, LDQ), rf1);
     }
