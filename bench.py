@@ -37,7 +37,7 @@ CHUNK = 64
 
 
 def gla_seg(bh: int, nc: int, dk: int, dv: int) -> int:
-    """Chunks per segment of the GLA state pass (the library's policy gla_plan for bf16 io; 0 =
+    """Chunks per segment of the GLA state pass (the library's policy gla_plan for bf16 io and gates; 0 =
     one segment): segment count and value columns per workgroup (64 or 128) that minimise
     rounds of 512 workgroups x chunks per segment x step cost plus the scan."""
     best, best_cost = 0, None

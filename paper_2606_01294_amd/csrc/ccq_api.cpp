@@ -152,7 +152,8 @@ FwdLayout fwd_layout(const ccq_shape* s, ccq_backbone bb) {
   L.clean = take_clean_ws(s, take);
   if (bb == CCQ_GLA) {
     const long long nc = (s->T + 63) / 64;
-    const ccq::GlaPlan plan = ccq::gla_plan((long long)s->B * s->H, nc, s->dk, s->dv, s->io_dtype == CCQ_BF16);
+    const ccq::GlaPlan plan = ccq::gla_plan((long long)s->B * s->H, nc, s->dk, s->dv, s->io_dtype == CCQ_BF16,
+                                            s->gate_dtype == CCQ_BF16);
     L.gla_seg = plan.seg;
     L.gla_vs = plan.vs;
     if (L.gla_seg > 0) {

@@ -596,7 +596,7 @@ hipError_t run_gla_state_v(const GlaStateArgs& a, hipStream_t st) {
 // 128-wide ones where gla_plan cut the sequence for them.
 template <typename T, typename TG, bool kRev = false>
 hipError_t run_gla_state(const GlaStateArgs& a, hipStream_t st) {
-  if constexpr (sizeof(T) == 2 && !kRev)
+  if constexpr (sizeof(T) == 2 && sizeof(TG) == 2 && !kRev)
     if (a.seg > 0 && a.vs == 128) return run_gla_state_v<T, TG, 8, kRev>(a, st);
   const long long waves64 = (long long)a.B * a.H * (a.dk / 64) * (a.dv / 64) * 4 * gla_nseg(a);
   if (waves64 >= 1024) return run_gla_state_v<T, TG, 4, kRev>(a, st);

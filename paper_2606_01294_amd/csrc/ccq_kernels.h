@@ -356,14 +356,16 @@ hipError_t launch_gla_scan(const GlaScanArgs& a, bool is_bf16, hipStream_t st);
 // of the segment totals and entry states (12 per element, at 4 TB/s); the fewest
 // segments on a tie.  State pass and scan together, 64 columns only against the
 // plan: 32 heads of 32 chunks, dk = 128, dv = 256: 44 -> 38 us; 4 heads of 320: 52
-// -> 43 us.
+// -> 43 us.  32-bit gates keep to 64 columns: a 128-wide workgroup's LDS (94 KB)
+// would be alone on its compute unit (whole forward, 32 heads of 64 chunks: 198 us
+// with 64 columns, 202 with 128).
 struct GlaPlan {
   int seg, vs;
 };
-inline GlaPlan gla_plan(long long bh, long long nc, int dk, int dv, bool is_bf16) {
+inline GlaPlan gla_plan(long long bh, long long nc, int dk, int dv, bool is_bf16, bool gate_bf16) {
   GlaPlan best{0, 64};
   long long best_cost = -1;
-  for (int vs = 64; vs <= (is_bf16 && dv % 128 == 0 ? 128 : 64); vs *= 2) {
+  for (int vs = 64; vs <= (is_bf16 && gate_bf16 && dv % 128 == 0 ? 128 : 64); vs *= 2) {
     const long long tiles = bh * (dk / 64) * (dv / vs);
     for (long long ns = 1; ns <= 64 && ns <= nc; ++ns) {
       const long long sl = (nc + ns - 1) / ns;
