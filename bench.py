@@ -284,13 +284,11 @@ KERNELS = {0: ["gla_state"] + CLEAN + ["clean_out", "gla_out"],
                                  "gdn_bwd_prep", "gdn_dstate", "gdn_bwd_chunk", "clean_dq",
                                  "ccq_dk"]}
 VARLEN_GDN = KERNELS[1]  # the forward kernels read the packed rows themselves
-KERNEL_SYMBOL = {"prep_scales": "prep_kernel (row scales)", "varlen_gather_qk": "varlen_copy_kernel", "varlen_gather_v": "varlen_copy_kernel",
-                 "varlen_gather_scalar": "varlen_copy_kernel", "varlen_scatter_o": "varlen_copy_kernel",
-                 "varlen_fix": "varlen_cache_fix_kernel", "prep": "prep_kernel", "decode": "decode_kernel", "decode_split": "decode_cbar_kernel+decode_s_kernel", "clean_gram": "clean_gram_kernel",
+KERNEL_SYMBOL = {"prep_scales": "prep_kernel (row scales)", "prep": "prep_kernel", "decode": "decode_kernel", "decode_split": "decode_cbar_kernel+decode_s_kernel", "clean_gram": "clean_gram_kernel",
                  "clean_prefix": "clean_prefix_kernel", "clean_out": "clean_out_kernel",
                  "clean_out_train": "clean_out_kernel", "clean_dq": "clean_out_kernel",
                  "gla_state": "gla_state_kernel", "gla_scan": "gla_scan_kernel", "gla_out": "gla_out_kernel",
-                 "gdn_tri": "gdn_tri_kernel", "gdn_state": "gdn_state_dma_kernel",
+                 "gdn_tri": "gdn_tri_kernel", "gdn_state": "gdn_wy_state_kernel (gdn_state_dma_kernel in large training batches)",
                  "gdn_out": "gdn_out_kernel", "gla_dstate": "gla_state_kernel (reverse)",
                  "gla_bwd_chunk": "gla_bwd_chunk_kernel",
                  "gdn_bwd_prep": "gdn_bwd_prep_kernel", "gdn_dstate": "gdn_dstate_kernel",
@@ -308,8 +306,8 @@ def _source(kernel: str) -> str:
         return "ccq_decode.hip"
     if kernel in ("prep", "prep_scales"):
         return "ccq_prep.hip"
-    if kernel.startswith("varlen"):
-        return "ccq_varlen.hip"
+    if kernel == "gdn_state":
+        return "ccq_gdn_wy.hip"
     if kernel.startswith("gdn"):
         return "ccq_gdn.hip"
     return "ccq_bwd.hip"
