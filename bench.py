@@ -186,19 +186,6 @@ def kernel_cost(kernel: str, w, io_bytes: int = 2, gate_bytes: int = 2):
     elif kernel == "ccq_dk":
         by = ntok * (3 * dk * io_bytes + 12 + 4 * dk + dk * io_bytes)
         fl = ntok * (6 * dk * dk + 8 * C * dk)
-    elif kernel.startswith("varlen_"):
-        # packed rows read and padded rows written (gathers), padded rows read and
-        # packed rows written (scatter); rows of H heads
-        real = getattr(w, "packed_rows", w.B * w.T)
-        pad = w.B * w.T
-        rb = {"varlen_gather_qk": dk * io_bytes, "varlen_gather_v": dv * io_bytes,
-              "varlen_gather_scalar": 4, "varlen_scatter_o": dv * io_bytes}.get(kernel, 0) * w.H
-        if kernel == "varlen_fix":
-            by, fl = BH * (dk * dk + dk) * 8, 0
-        elif kernel == "varlen_scatter_o":
-            by, fl = 2 * real * rb, 0
-        else:
-            by, fl = (real + pad) * rb, 0
     else:
         raise KeyError(kernel)
     return by, fl
