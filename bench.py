@@ -275,7 +275,7 @@ KERNEL_SYMBOL = {"prep_scales": "prep_kernel (row scales)", "prep": "prep_kernel
                  "clean_prefix": "clean_prefix_kernel", "clean_out": "clean_out_kernel",
                  "clean_out_train": "clean_out_kernel", "clean_dq": "clean_out_kernel",
                  "gla_state": "gla_state_kernel", "gla_scan": "gla_scan_kernel", "gla_out": "gla_out_kernel",
-                 "gdn_tri": "gdn_tri_kernel", "gdn_state": "gdn_wy_state_kernel (gdn_state_dma_kernel in large training batches)",
+                 "gdn_tri": "gdn_tri_kernel", "gdn_state": "gdn_state_roles_kernel",
                  "gdn_out": "gdn_out_kernel", "gla_dstate": "gla_state_kernel (reverse)",
                  "gla_bwd_chunk": "gla_bwd_chunk_kernel",
                  "gdn_bwd_prep": "gdn_bwd_prep_kernel", "gdn_dstate": "gdn_dstate_kernel",
@@ -294,7 +294,7 @@ def _source(kernel: str) -> str:
     if kernel in ("prep", "prep_scales"):
         return "ccq_prep.hip"
     if kernel == "gdn_state":
-        return "ccq_gdn_wy.hip"
+        return "ccq_gdn_roles.hip"
     if kernel.startswith("gdn"):
         return "ccq_gdn.hip"
     return "ccq_bwd.hip"

@@ -129,11 +129,6 @@ struct FwdLayout {
   CleanWs clean;
 };
 
-// Whether the Gated DeltaNet state pass runs in WY form.
-bool use_wy(const ccq_shape* s, bool every_state) {
-  return ccq::gdn_wy((long long)s->B * s->H, (s->T + 63) / 64, s->dk, s->dv, s->io_dtype == CCQ_BF16, every_state);
-}
-
 // q_clean, the chunk-entry states S_r and, for Gated DeltaNet, the chunk
 // transforms Tm, the cumulative log decays and the corrected values U.
 FwdLayout fwd_layout(const ccq_shape* s, ccq_backbone bb) {
@@ -143,12 +138,8 @@ FwdLayout fwd_layout(const ccq_shape* s, ccq_backbone bb) {
   const size_t e = esize(s->io_dtype);
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off += align_up(bytes); return o; };
-  L.states = take(nchunk * s->dv * s->dk * e);
-  // W of the Gated DeltaNet WY state pass (nchunk * 64 * dk elements) lies over
-  // q_clean and the segment Grams behind it, which are written after that pass
-  // has read it: the last chunk's rows past the sequence's end (fewer than 64
-  // per head) fit in the head's first Gram (dk * dk fp32)
   L.qclean = take(ntok * s->dk * e);
+  L.states = take(nchunk * s->dv * s->dk * e);
   L.clean = take_clean_ws(s, take);
   if (bb == CCQ_GLA) {
     const long long nc = (s->T + 63) / 64;
@@ -323,16 +314,10 @@ ccq_status run_forward(ccq_backbone bb, const ccq_shape* s, const void* q, const
   trace_begin_call();
   // the backbone's chunk transforms (Gated DeltaNet) and state pass: chunk-entry
   // states S_r (and U)
-  const bool wy = bb == CCQ_GDN && use_wy(s, false);
   if (bb == CCQ_GDN) {
     ccq::TriArgs ta{k, la, beta, ws + L.Tm, gam, s->B, s->T, s->H, s->dk, s->dv};
     ta.cu = cu;
     ta.rk = rk;
-    if (wy) {
-      ta.W = qclean;
-      ta.Tb = ws + L.Tm;
-      ta.Tm = nullptr;
-    }
     if (traced(st, [&] { return ccq::launch_gdn_tri(ta, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   }
   if (bb == CCQ_GLA) {
@@ -362,13 +347,7 @@ ccq_status run_forward(ccq_backbone bb, const ccq_shape* s, const void* q, const
                     s->dk, s->dv};
     da.sstride = ccq::gdn_out_group(s->B, s->H, s->T, s->dk, s->dv, bf);  // one state per output group
     da.cu = cu;
-    if (wy) {
-      da.W = qclean;
-      da.Tb = ws + L.Tm;
-    }
-    if (traced(st, [&] { return wy ? ccq::launch_gdn_wy_state(da, st) : ccq::launch_gdn_state(da, bf, st); }) !=
-        hipSuccess)
-      return CCQ_ERR_HIP;
+    if (traced(st, [&] { return ccq::launch_gdn_state(da, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   }
 
   // the query contraction
@@ -447,16 +426,8 @@ ccq_status gdn_fwd_bwd(const ccq_shape* s, const int32_t* cu, const void* q, con
   ccq::GdnArgs sa{k, v, beta, ws + L.Tm, gam, nullptr, nullptr, ws + L.states, ws + L.U, s->B,
                   s->T, s->H, s->dk, s->dv};
   sa.cu = cu;
-  const bool wy = use_wy(s, true);
-  if (wy) {
-    // in buffers that are written after the state pass: W in dS (dv >= 64), Tb in Tm^T
-    sa.W = ta.W = ws + L.dstates;
-    sa.Tb = ta.Tb = ws + L.TmT;
-  }
   if (traced(st, [&] { return ccq::launch_gdn_tri(ta, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
-  if (traced(st, [&] { return wy ? ccq::launch_gdn_wy_state(sa, st) : ccq::launch_gdn_state(sa, bf, st); }) !=
-      hipSuccess)
-    return CCQ_ERR_HIP;
+  if (traced(st, [&] { return ccq::launch_gdn_state(sa, bf, st); }) != hipSuccess) return CCQ_ERR_HIP;
   ccq::GdnOutArgs oa{ws + L.qclean, k, gam, ws + L.states, ws + L.U, o, s->B, s->T, s->H, s->dk,
                      s->dv, s->scale};
   oa.cu = cu;

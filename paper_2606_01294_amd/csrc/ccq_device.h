@@ -590,6 +590,8 @@ struct LdsStream {
 // pieces per row is kept at p ^ kswz(r), which keeps row-fragment and
 // transposing reads free of bank conflicts.
 __device__ __forceinline__ int kswz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
+// The same for tiles of eight pieces per row.
+__device__ __forceinline__ int tswz(int r) { return (r >> 1) & 7; }
 
 template <int X>
 __device__ __forceinline__ void wait_vm() {

@@ -15,8 +15,10 @@
 //   S_{r+1} = e^{gamma_C} S_r + U^T diag(e^{gamma_C - gamma}) K.
 //
 // gdn_tri_kernel forms Tm for every chunk in parallel (MFMA block inversion in
-// fp32); gdn_state_kernel walks the chunks of one head in order, keeping a
-// slice of S in MFMA accumulators, and stores S_r and U for every chunk;
+// fp32); gdn_state_kernel (fp32, and bf16 with dk = 64; gdn_state_roles_kernel
+// in ccq_gdn_roles.hip with dk = 128 and 256) walks the chunks of one head in
+// order, keeping a slice of S in MFMA accumulators, and stores S_r and U for
+// every chunk;
 // gdn_out_kernel then forms the outputs of all chunks in parallel.  S_r and
 // U^T are stored fragment-native: per 16-row value tile and 32-wide k step a
 // contiguous 16 x 32 block, so the state kernel writes and the output kernel
@@ -34,19 +36,8 @@ namespace ccq {
 // sequential state pass needs no exponentials.
 // Blocks of 16: the diagonal blocks are inverted by forward substitution,
 // then wave w forms column block w, X_iw = -D_i sum_{m=w}^{i-1} A_im X_mw.
-//
-// kWY also forms the operands of the WY state pass (gdn_wy_state_kernel), both
-// lane-native (16 bytes per lane, 1 KB per block, in the order a 16-row MFMA
-// operand is read): Tb = Tm diag(beta), the six blocks (I, kq) that are not
-// zero, and W = -Tm diag(beta e^gamma) K, blocks (I, m) of token tile I and 32
-// features m.  K stays in registers from its staging and takes the place of A and X
-// once they are operand fragments, so the workgroup needs no more LDS.
-//
-// Bound by memory from dk = 128 (K read, with kWY W written: 36 us for 134 MB at
-// 2048 chunks of dk = 256, 25 us without W); four workgroups per compute unit,
-// which the register bound keeps (136 registers without it).
-template <typename T, int DK, bool kWY>
-__global__ __launch_bounds__(kThreads, 4) void gdn_tri_kernel(const TriArgs a) {
+template <typename T, int DK>
+__global__ __launch_bounds__(kThreads) void gdn_tri_kernel(const TriArgs a) {
   constexpr int C = kChunk;
   constexpr int P = Pad<T>::value;
   constexpr int LDQ = DK + P;
@@ -60,7 +51,6 @@ __global__ __launch_bounds__(kThreads, 4) void gdn_tri_kernel(const TriArgs a) {
   float* const sX = sA + C * LDA;
   __shared__ __align__(16) float sY[4][16 * 17];
   __shared__ __align__(16) float sGam[C], sBeta[C];
-  __shared__ __align__(16) float sBg[kWY ? C : 4];  // -beta_j e^{gamma_j}
 
   const int N = (a.T + C - 1) / C;
   const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
@@ -98,7 +88,6 @@ __global__ __launch_bounds__(kThreads, 4) void gdn_tri_kernel(const TriArgs a) {
     const float gC = __shfl(x, C - 1);
     sGam[tid] = x;
     sBeta[tid] = bt;
-    if constexpr (kWY) sBg[tid] = -bt * __expf(x);
     float* cf = a.gam + ((size_t)bh * N + ci) * 5 * C + tid;
     cf[0] = x;                      // gamma_j
     // (with raw keys the two coefficients that multiply key rows carry the
@@ -178,64 +167,15 @@ __global__ __launch_bounds__(kThreads, 4) void gdn_tri_kernel(const TriArgs a) {
   // Tm rows i, each 32-column block in acc_pos order: positions 8q .. 8q + 7
   // of a row hold logical columns b + 4 (q % 4) .. + 3 and b + 16 + 4 (q % 4)
   // .. + 3 (b = the block's first column), two 16-byte LDS reads per piece
-  if (!kWY || a.Tm) {
-    T* Tout = static_cast<T*>(a.Tm) + ((size_t)bh * N + ci) * C * C;
-    for (int idx = tid; idx < C * C / 8; idx += kThreads) {
-      const int i = idx / (C / 8), q = idx % (C / 8);
-      const int lc = ((8 * q) & ~31) + 4 * (q & 3);
-      f32x4 lo = *reinterpret_cast<const f32x4*>(sX + i * LDA + lc);
-      f32x4 hi = *reinterpret_cast<const f32x4*>(sX + i * LDA + lc + 16);
-      if ((lc >> 4) > (i >> 4)) lo = zero4();  // above the diagonal blocks
-      if (((lc + 16) >> 4) > (i >> 4)) hi = zero4();
-      store_acc_pair(Tout + i * C + 8 * q, lo, hi);
-    }
-  }
-
-  if constexpr (kWY) {
-    // lane's entries of block (I, kq): row 16 I + c16, columns
-    // 32 kq + 4 g4 .. + 3 and 32 kq + 16 + 4 g4 .. + 3 (rows of tiles 0 and 1
-    // end in the first block of columns), times the columns' coefficients
-    auto block = [&](int I, int kq, const float* cf) {
-      const int lc = 32 * kq + 4 * g4;
-      f32x4 x = *reinterpret_cast<const f32x4*>(sX + (16 * I + c16) * LDA + lc);
-      f32x4 y = *reinterpret_cast<const f32x4*>(sX + (16 * I + c16) * LDA + lc + 16);
-      x *= *reinterpret_cast<const f32x4*>(cf + lc);
-      y *= *reinterpret_cast<const f32x4*>(cf + lc + 16);
-      if (2 * kq > I) x = zero4();
-      if (2 * kq + 1 > I) y = zero4();
-      return acc_pair_frag<T>(x, y);
-    };
-    T* tb = static_cast<T*>(a.Tb) + ((size_t)bh * N + ci) * (kTbBytes / 2) + 8 * l;
-    const int tb0 = w < 2 ? w : 2 * w - 2;  // (0, 0), (1, 0), (2, 0), (2, 1), (3, 0), (3, 1)
-    store_frag(tb + tb0 * 512, block(w, 0, sBeta));
-    if (w >= 2) store_frag(tb + (tb0 + 1) * 512, block(w, 1, sBeta));
-    Frag<T> tw[4][2];
-#pragma unroll
-    for (int I = 0; I < 4; ++I) {
-      tw[I][0] = block(I, 0, sBg);
-      if (I >= 2) tw[I][1] = block(I, 1, sBg);
-    }
-    __syncthreads();  // A and X are in registers: K takes their place
-    rk.store(sK, LDQ);
-    __syncthreads();
-    T* wout = static_cast<T*>(a.W) + ((size_t)bh * N + ci) * C * DK + 8 * l;
-    for (int m = w; m < DK / 32; m += kThreads / 64) {
-      Frag<T> kf[2][2];
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-        for (int kq = 0; kq < 2; ++kq) kf[hh][kq] = ld_frag_tr_acc_pair(sK + 32 * kq * LDQ, LDQ, 2 * m + hh);
-#pragma unroll
-      for (int I = 0; I < 4; ++I) {
-        f32x4 x = zero4(), y = zero4();
-#pragma unroll
-        for (int kq = 0; kq < (I >= 2 ? 2 : 1); ++kq) {
-          mma(x, kf[0][kq], tw[I][kq]);
-          mma(y, kf[1][kq], tw[I][kq]);
-        }
-        store_frag(wout + (I * (DK / 32) + m) * 512, acc_pair_frag<T>(x, y));
-      }
-    }
+  T* Tout = static_cast<T*>(a.Tm) + ((size_t)bh * N + ci) * C * C;
+  for (int idx = tid; idx < C * C / 8; idx += kThreads) {
+    const int i = idx / (C / 8), q = idx % (C / 8);
+    const int lc = ((8 * q) & ~31) + 4 * (q & 3);
+    f32x4 lo = *reinterpret_cast<const f32x4*>(sX + i * LDA + lc);
+    f32x4 hi = *reinterpret_cast<const f32x4*>(sX + i * LDA + lc + 16);
+    if ((lc >> 4) > (i >> 4)) lo = zero4();  // above the diagonal blocks
+    if (((lc + 16) >> 4) > (i >> 4)) hi = zero4();
+    store_acc_pair(Tout + i * C + 8 * q, lo, hi);
   }
 }
 
@@ -460,427 +400,6 @@ __global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_state_kernel(const GdnAr
   }
 }
 
-// The same recurrence for bf16 with the chunk operands streamed straight into
-// LDS (global_load_lds_dwordx4), NSTAGE - 1 chunks ahead, through a ring of
-// NSTAGE stages: K (64 x DK), Tm (64 x 64), the V slice (64 x BVS) and the
-// four coefficient rows.  No registers hold prefetched data and no
-// instructions copy it; the vector-memory counter is waited on explicitly,
-// with the chunk stores of the NSTAGE - 1 previous chunks allowed to remain in
-// flight.  Rows are
-// unpadded, so K and Tm are stored with their 16-byte pieces permuted per row
-// (an XOR of the piece index) to keep the fragment reads free of bank
-// conflicts: piece p of K row r sits at p ^ kswz(r), of Tm row r at p ^ tswz(r).
-__device__ __forceinline__ int tswz(int r) { return (r >> 1) & 7; }
-
-// s_waitcnt vmcnt(n) for a wave-uniform n in 0..47 (the counter field is an
-// immediate: one scalar branch to the matching wait)
-__device__ __forceinline__ void wait_vm_n(int n) {
-  switch (n) {
-#define CCQ_WAIT_CASE(i) \
-  case i:                \
-    wait_vm<i>();        \
-    break;
-#define CCQ_WAIT_CASE8(i) \
-  CCQ_WAIT_CASE(i) CCQ_WAIT_CASE(i + 1) CCQ_WAIT_CASE(i + 2) CCQ_WAIT_CASE(i + 3) CCQ_WAIT_CASE(i + 4) \
-  CCQ_WAIT_CASE(i + 5) CCQ_WAIT_CASE(i + 6) CCQ_WAIT_CASE(i + 7)
-    CCQ_WAIT_CASE8(0) CCQ_WAIT_CASE8(8) CCQ_WAIT_CASE8(16) CCQ_WAIT_CASE8(24) CCQ_WAIT_CASE8(32) CCQ_WAIT_CASE8(40)
-#undef CCQ_WAIT_CASE8
-#undef CCQ_WAIT_CASE
-    default:
-      wait_vm<0>();
-      break;
-  }
-}
-
-// RS (reduce-scatter exchange): instead of every wave of a value tile reading
-// all NH x 4 partial products and forming all of R, wave hq sums the partials
-// of its own 4 / NH token tiles (the same fixed order), forms those tiles of R
-// from its own rows of V and of the coefficients, and writes them as bf16 in
-// the layout of the operand fragments of U = Tm R; after a second barrier every
-// wave reads the two fragments.  R enters the product as bf16 either way.
-// RSU (with RS): U = Tm R is split the same way: wave hq forms only the rows
-// of its own token tiles, stores them as its part of U^T, and shares them,
-// times e^{gamma_C - gamma}, as bf16 operand fragments for the state update.
-template <int DK, int NPR, int NH, int NSTAGE, bool RS = false, bool RSU = false>
-__global__ __launch_bounds__(64 * NPR * NH, 1) void gdn_state_dma_kernel(const GdnArgs a) {
-  typedef bf16_t T;
-  typedef __attribute__((address_space(3))) void lds_void;
-  constexpr int C = kChunk, NW = NPR * NH, BVS = 16 * NPR;
-  constexpr int DKH = DK / NH, NCT = DKH / 16, NKH = DKH / 32;
-  constexpr int RB = DK * 2;                                  // K row bytes
-  constexpr int KB = C * RB, TB = C * C * 2, VB = C * BVS * 2, FB = 4 * C * 4;
-  constexpr int NIK = KB / 1024, NIT = TB / 1024, NIV = VB / 1024;
-  constexpr int NIVW = (NIV + NW - 1) / NW;                   // V pieces per wave (some idle)
-  constexpr int NIW = NIK / NW + NIT / NW + NIVW + 1;         // 1 KB pieces per wave and chunk
-  constexpr int SB = KB + TB + VB + FB;
-  constexpr int XB = NH > 1 ? NW * 4 * 64 * 16 : 16;
-  constexpr int XR = (RS ? NPR * 2 * 64 * 16 : 0) * (RSU ? 2 : 1);  // bf16 R (RSU: and U) fragments
-  constexpr int NSU = NH == 1 ? 2 : 1;                         // U^T stores per wave per chunk
-  static_assert(DK == 128 || DK == 256, "key width");
-  static_assert(NH == 1 || NH == 2 || NH == 4, "key split");
-  static_assert(NSTAGE == 2 || NSTAGE == 3, "ring depth");
-  static_assert(NKH >= 1 && VB % 1024 == 0, "tiles");
-  static_assert(!RS || NH > 1, "the reduce-scatter exchange splits the keys");
-  static_assert(!RSU || RS, "the split U builds on the split R");
-  static_assert(NIV % NW == 0 || NW % NIV == 0, "V pieces over the waves");
-  __shared__ __align__(1024) char smem[NSTAGE * SB + XB + XR];
-  f32x4* const sX = reinterpret_cast<f32x4*>(smem + NSTAGE * SB);
-  T* const sR = reinterpret_cast<T*>(smem + NSTAGE * SB + XB);
-  T* const sU = sR + NPR * 2 * 64 * 8;  // RSU: fragments of U diag(e^{gamma_C - gamma})
-
-  const int nvt = a.dv / BVS;
-  const int N = (a.T + C - 1) / C;
-  const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
-  // heads in head-major order: the workgroups of consecutive logical blocks
-  // (one compute-unit cluster) then hold one head of every sequence, which
-  // balances the clusters when a packed batch's sequences differ in length
-  const int hm = lb / nvt;
-  const int bh = (hm % a.B) * a.H + hm / a.B;
-  const int l = lane_id(), g4 = l >> 4, c16 = l & 15;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int pr = w / NH, hq = w % NH;
-  const int v0 = (lb % nvt) * BVS;
-  const int v = v0 + 16 * pr + c16;
-  const int c0 = hq * DKH;
-  const int b = bh / a.H, h = bh % a.H;
-  const Seq sq = seq_of(a.cu, b, a.T);
-  const int NL = (sq.len + C - 1) / C;  // chunks walked (a packed sequence's own)
-  const T* k = static_cast<const T*>(a.k);
-  const T* vin = static_cast<const T*>(a.v);
-  const T* Tg = static_cast<const T*>(a.Tm);
-
-  // chunk ci into stage ci % NSTAGE.  Piece i of each operand goes to wave
-  // i % NW, so every wave issues the same number of pieces of each kind (a
-  // piece that not every wave can have is shared out by lanes).  Addresses
-  // are a per-chunk base (uniform) plus a 32-bit per-lane offset; rows past
-  // the end of the sequence read row nrow - 1 (finite data; the chunk
-  // transform zeroes their contribution).
-  static_assert(NIK % NW == 0 && NIT % NW == 0 && 64 % NW == 0, "piece split");
-  // the K pieces [it0, it1) of this wave
-  auto issue_k = [&](int ci, int it0, int it1) {
-    char* sb = smem + (ci % NSTAGE) * SB;
-    const int r0 = ci * C, nrow = min(C, sq.len - r0);
-    const int hs = a.H * DK;
-    const T* kb = k + seq_off(sq, r0, h, a.H, DK);
-#pragma unroll
-    for (int it = 0; it < NIK / NW; ++it) {
-      if (it < it0 || it >= it1) continue;
-      constexpr int CPR = DK / 8;
-      const int ins = it * NW + w, row = ins * (64 / CPR) + l / CPR;
-      const int off = min(row, nrow - 1) * hs + 8 * ((l % CPR) ^ kswz(row));
-      __builtin_amdgcn_global_load_lds((const void*)(kb + off), (lds_void*)(sb + ins * 1024), 16, 0, 0);
-    }
-  };
-  // the Tm, V and coefficient pieces of this wave
-  auto issue_rest = [&](int ci) {
-    char* sb = smem + (ci % NSTAGE) * SB;
-    const int r0 = ci * C, nrow = min(C, sq.len - r0);
-    const int hv = a.H * a.dv;
-    const T* tb = Tg + ((size_t)bh * N + ci) * C * C;
-    const T* vb = vin + seq_off(sq, r0, h, a.H, a.dv) + v0;
-#pragma unroll
-    for (int it = 0; it < NIT / NW; ++it) {
-      const int ins = it * NW + w, row = ins * 8 + l / 8;
-      const int off = row * C + 8 * ((l % 8) ^ tswz(row));
-      __builtin_amdgcn_global_load_lds((const void*)(tb + off), (lds_void*)(sb + KB + ins * 1024), 16, 0, 0);
-    }
-    {
-      // with fewer V pieces than waves, NW / NIV waves share a piece, each
-      // loading its own lanes of it (lane i of a piece lands at its base + 16 i
-      // whichever lanes are active)
-      constexpr int CPR = BVS / 8, SH = NIV >= NW ? 1 : NW / NIV, LPW = 64 / SH;
-#pragma unroll
-      for (int it = 0; it < NIVW; ++it) {
-        const int ins = SH == 1 ? it * NW + w : w / SH, row = ins * (64 / CPR) + l / CPR;
-        if (SH == 1 || l / LPW == w % SH) {
-          const int off = min(row, nrow - 1) * hv + 8 * (l % CPR);
-          __builtin_amdgcn_global_load_lds((const void*)(vb + off), (lds_void*)(sb + KB + TB + ins * 1024), 16, 0, 0);
-        }
-      }
-    }
-    // the coefficient rows, one piece shared the same way by all the waves
-    if (l / (64 / NW) == w)
-      __builtin_amdgcn_global_load_lds((const void*)(a.gam + (((size_t)bh * N + ci) * 5 + 1) * C + 4 * l),
-                                       (lds_void*)(sb + KB + TB + VB), 16, 0, 0);
-  };
-  auto issue = [&](int ci) {
-    issue_k(ci, 0, NIK / NW);
-    issue_rest(ci);
-  };
-  // stores per wave of chunk c: S_r (every sstride-th chunk) and U^T
-  auto nstore = [&](int c) { return (c % a.sstride == 0 ? NKH : 0) + NSU; };
-  // wait until chunk ci has landed: the pieces and stores issued after its own
-  // may stay in flight (three stages: stores of chunk ci - 2, pieces of
-  // ci + 1, stores of ci - 1; two stages: stores of ci - 1)
-  auto wait_chunk = [&](int ci) {
-    int n = ci >= 1 ? nstore(ci - 1) : 0;
-    if constexpr (NSTAGE == 3) n += (ci >= 2 ? nstore(ci - 2) : 0) + (ci + 1 < NL ? NIW : 0);
-    wait_vm_n(n);
-  };
-
-#pragma unroll
-  for (int s = 0; s < NSTAGE - 1; ++s)
-    if (s < NL) issue(s);
-
-  // S^T[c][v] in pair order: c = c0 + pair_feat(tc, g4) + r, so that the
-  // packed operand of tiles 2m, 2m + 1 holds 8 consecutive features per lane
-  // group (the states are stored so, and K is read with plain 16-byte reads)
-  f32x4 S[NCT];
-#pragma unroll
-  for (int tc = 0; tc < NCT; ++tc) {
-    if (a.S0)
-      S[tc] = *reinterpret_cast<const f32x4*>(a.S0 + ((size_t)bh * a.dv + v) * DK + c0 + pair_feat(tc, g4));
-    else
-      S[tc] = zero4();
-  }
-
-  const int vt = (v0 >> 4) + pr;
-  T* st_base = static_cast<T*>(a.states) + (((size_t)vt * (DK / 32) + hq * NKH) * 16 + c16) * 32 + 8 * g4;
-  T* u_base = static_cast<T*>(a.U) + ((size_t)vt * 2 * 16 + c16) * 32 + 8 * g4;
-
-  for (int ci = 0; ci < NL; ++ci) {
-    const char* sb = smem + (ci % NSTAGE) * SB;
-    const char* Kb = sb;
-    const T* Tb = reinterpret_cast<const T*>(sb + KB);
-    const T* Vb = reinterpret_cast<const T*>(sb + KB + TB);
-    const float* Fb = reinterpret_cast<const float*>(sb + KB + TB + VB);
-    wait_chunk(ci);
-    lds_barrier();  // chunk ci visible; stage (ci - 1) % NSTAGE and the exchange area released
-    // chunk ci + NSTAGE - 1 goes out in pieces between this chunk's first
-    // products (their issue then overlaps the matrix cores' work), all of it
-    // before this chunk's stores, so the counted waits stay as they are
-    const bool ahead = ci + NSTAGE - 1 < NL;
-    constexpr int KPJ = (NIK / NW + 3) / 4;  // K pieces after each token tile of P
-
-    // P = K S_r^T over this wave's features: K rows 16 J + c16, features in
-    // natural order (piece (c0 + 32 m) / 8 + g4, one 16-byte read)
-    Frag<T> sf[NKH];
-#pragma unroll
-    for (int m = 0; m < NKH; ++m) sf[m] = acc_pair_frag<T>(S[2 * m], S[2 * m + 1]);
-    const int ks = kswz(c16);
-    auto kfrag = [&](int J, int m) {
-      const char* row = Kb + (16 * J + c16) * RB;
-      const int p0 = (c0 + 32 * m) / 8 + g4;
-      Frag<T> f;
-      f.v = *reinterpret_cast<const bf16x8*>(row + 16 * (p0 ^ ks));
-      return f;
-    };
-    // the V slice, transposed (issued now, waited for where used); RS: the
-    // rows of this wave's token tiles only (tile J is rows 16 J + 4 g4 + r)
-    constexpr int JPW = RS ? 4 / NH : 4;
-    const int J0 = RS ? hq * JPW : 0;
-    Frag<T> vf[2];
-    bf16x4 vw[RS ? JPW : 1];
-    {
-      const int j = c16;
-      const char* pv = reinterpret_cast<const char*>(Vb) + (4 * g4 + (j >> 2)) * (2 * BVS) + 32 * pr + 8 * (j & 3);
-      if constexpr (RS) {
-#pragma unroll
-        for (int jj = 0; jj < JPW; ++jj) vw[jj] = ds_read_tr16_asm(pv + 16 * (J0 + jj) * 2 * BVS);
-      } else {
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          const bf16x4 lo = ds_read_tr16_asm(pv + 32 * m * 2 * BVS);
-          const bf16x4 hi = ds_read_tr16_asm(pv + (32 * m + 16) * 2 * BVS);
-          vf[m].v = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        }
-      }
-    }
-    f32x4 R[4];
-    {
-      Frag<T> kf[2][NKH];
-#pragma unroll
-      for (int m = 0; m < NKH; ++m) kf[0][m] = kfrag(0, m);
-#pragma unroll
-      for (int J = 0; J < 4; ++J) {
-        if (J + 1 < 4)
-#pragma unroll
-          for (int m = 0; m < NKH; ++m) kf[(J + 1) & 1][m] = kfrag(J + 1, m);
-        __builtin_amdgcn_sched_barrier(0);
-        f32x4 acc = zero4();
-#pragma unroll
-        for (int m = 0; m < NKH; ++m) mma(acc, kf[J & 1][m], sf[m]);
-        R[J] = acc;
-        if (ahead) issue_k(ci + NSTAGE - 1, J * KPJ, (J + 1) * KPJ);
-      }
-    }
-    if (ahead) issue_rest(ci + NSTAGE - 1);
-    // coefficients and Tm rows, read now so that their latency overlaps the
-    // exchange
-    constexpr int IPW = RSU ? JPW : 4;  // the token tiles of U this wave forms
-    const int I0 = RSU ? J0 : 0;
-    Frag<T> tfr[IPW][2];
-    f32x4 bg[JPW], bj[JPW], dd[IPW];  // bg, bj: the token tiles this wave forms R for
-#pragma unroll
-    for (int jj = 0; jj < JPW; ++jj) {
-      bg[jj] = *reinterpret_cast<const f32x4*>(Fb + 16 * (J0 + jj) + 4 * g4);
-      bj[jj] = *reinterpret_cast<const f32x4*>(Fb + C + 16 * (J0 + jj) + 4 * g4);
-    }
-#pragma unroll
-    for (int ii = 0; ii < IPW; ++ii) dd[ii] = *reinterpret_cast<const f32x4*>(Fb + 2 * C + 16 * (I0 + ii) + 4 * g4);
-    const float eC = Fb[3 * C];
-    {
-      const int ts = tswz(c16);
-#pragma unroll
-      for (int ii = 0; ii < IPW; ++ii)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          tfr[ii][q].v = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(Tb) +
-                                                          (16 * (I0 + ii) + c16) * 128 + 16 * ((4 * q + g4) ^ ts));
-    }
-    Frag<T> rf0, rf1;  // R as the bf16 operand of U = Tm R (tiles 0, 1 and 2, 3)
-    if constexpr (RS) {
-      // this wave's token tiles: the NH partials summed in the fixed order,
-      // R = beta V - beta e^gamma P, written as bf16 where fragment J / 2 of the
-      // slice keeps tile J in its lane's elements 4 (J % 2) .. + 3
-#pragma unroll
-      for (int J = 0; J < 4; ++J) sX[(w * 4 + J) * 64 + l] = R[J];
-      lds_barrier();  // (also completes this wave's V and coefficient reads)
-#pragma unroll
-      for (int jj = 0; jj < JPW; ++jj) asm volatile("" : "+v"(vw[jj]));
-#pragma unroll
-      for (int jj = 0; jj < JPW; ++jj) {
-        const int J = J0 + jj;
-        f32x4 sum = sX[((pr * NH) * 4 + J) * 64 + l];
-#pragma unroll
-        for (int hh = 1; hh < NH; ++hh) sum += sX[((pr * NH + hh) * 4 + J) * 64 + l];
-        bf16x4 y;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) y[r] = static_cast<bf16_t>(bj[jj][r] * f32(vw[jj][r]) - bg[jj][r] * sum[r]);
-        *reinterpret_cast<bf16x4*>(sR + ((pr * 2 + (J >> 1)) * 64 + l) * 8 + 4 * (J & 1)) = y;
-      }
-      lds_barrier();
-      rf0.v = *reinterpret_cast<const bf16x8*>(sR + ((pr * 2) * 64 + l) * 8);
-      rf1.v = *reinterpret_cast<const bf16x8*>(sR + ((pr * 2 + 1) * 64 + l) * 8);
-    } else if constexpr (NH > 1) {
-      // sum the NH partial products of this value slice, in a fixed order so
-      // every wave of the slice holds bit-identical P
-#pragma unroll
-      for (int J = 0; J < 4; ++J) sX[(w * 4 + J) * 64 + l] = R[J];
-      lds_barrier();
-      f32x4 part[NH][4];
-#pragma unroll
-      for (int hh = 0; hh < NH; ++hh)
-#pragma unroll
-        for (int J = 0; J < 4; ++J) part[hh][J] = sX[((pr * NH + hh) * 4 + J) * 64 + l];
-#pragma unroll
-      for (int J = 0; J < 4; ++J) {
-        f32x4 sum = part[0][J];
-#pragma unroll
-        for (int hh = 1; hh < NH; ++hh) sum += part[hh][J];
-        R[J] = sum;
-      }
-    }
-    // K^T of this wave's features for the update, in the pair order of the
-    // state tiles (rows 4 g4 + j / 4 (+ 16) of each 32-token half, features
-    // c0 + pair_feat(t, j % 4): piece (c0 + 32 (t / 2)) / 8 + j % 4, half t % 2),
-    // issued now so that they arrive while R and U are formed
-    Frag<T> tf[NCT][2];
-    {
-      const int j = c16, rr = 4 * g4 + (j >> 2), rs = kswz(rr);
-#pragma unroll
-      for (int t = 0; t < NCT; ++t)
-#pragma unroll
-        for (int kq = 0; kq < 2; ++kq) {
-          const int p = (c0 + 32 * (t >> 1)) / 8 + (j & 3), hb = (t & 1) * 8;
-          const char* pl = Kb + (32 * kq + rr) * RB + 16 * (p ^ rs) + hb;
-          const bf16x4 lo = ds_read_tr16_asm(pl);
-          const bf16x4 hi = ds_read_tr16_asm(pl + 16 * RB);
-          tf[t][kq].v = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        }
-    }
-    if constexpr (!RS) {
-      lds_wait_but<(4 * NCT < 15 ? 4 * NCT : 15)>(vf);  // at most 15 LDS reads stay in flight
-      // R = beta V - beta e^gamma P
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int J = 2 * m + hh;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) R[J][r] = bj[J][r] * frag_elem(vf[m], 4 * hh + r) - bg[J][r] * R[J][r];
-        }
-      rf0 = acc_pair_frag<T>(R[0], R[1]);
-      rf1 = acc_pair_frag<T>(R[2], R[3]);
-    }
-    // U = Tm R (Tm rows are stored in acc_pos order)
-    f32x4 U[IPW];
-#pragma unroll
-    for (int ii = 0; ii < IPW; ++ii) {
-      U[ii] = zero4();
-      mma(U[ii], tfr[ii][0], rf0);
-      mma(U[ii], tfr[ii][1], rf1);
-    }
-    Frag<T> uf[2], ud0, ud1;
-    bf16x4 uw[IPW];  // RSU: this wave's tiles of U as bf16, its part of U^T
-    if constexpr (RSU) {
-      // tile I lives in elements 4 (I % 2) .. + 3 of fragment I / 2
-#pragma unroll
-      for (int ii = 0; ii < IPW; ++ii) {
-        const int I = I0 + ii;
-        bf16x4 y;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          uw[ii][r] = static_cast<bf16_t>(U[ii][r]);
-          y[r] = static_cast<bf16_t>(U[ii][r] * dd[ii][r]);
-        }
-        *reinterpret_cast<bf16x4*>(sU + ((pr * 2 + (I >> 1)) * 64 + l) * 8 + 4 * (I & 1)) = y;
-      }
-      lds_barrier();
-      ud0.v = *reinterpret_cast<const bf16x8*>(sU + ((pr * 2) * 64 + l) * 8);
-      ud1.v = *reinterpret_cast<const bf16x8*>(sU + ((pr * 2 + 1) * 64 + l) * 8);
-    } else {
-      uf[0] = acc_pair_frag<T>(U[0], U[1]);
-      uf[1] = acc_pair_frag<T>(U[2], U[3]);
-#pragma unroll
-      for (int I = 0; I < 4; ++I) U[I] *= dd[I];
-      ud0 = acc_pair_frag<T>(U[0], U[1]);
-      ud1 = acc_pair_frag<T>(U[2], U[3]);
-    }
-    // S^T <- e^{gamma_C} S^T + K^T diag(e^{gamma_C - gamma}) U
-#pragma unroll
-    for (int t = 1; t < NCT; ++t) lds_wait(tf[t]);
-#pragma unroll
-    for (int tc = 0; tc < NCT; ++tc) {
-      S[tc] *= eC;
-      mma(S[tc], tf[tc][0], ud0);
-      mma(S[tc], tf[tc][1], ud1);
-    }
-    // S_r and U^T of this chunk, fragment-native (1 KB per value tile and k step)
-    {
-      T* st_out = st_base + ((size_t)bh * N + ci) * a.dv * DK;
-      if (ci % a.sstride == 0)
-#pragma unroll
-        for (int m = 0; m < NKH; ++m) store_frag(st_out + 16 * 32 * m, sf[m]);
-      T* u_out = u_base + ((size_t)bh * N + ci) * a.dv * C;
-      if constexpr (RSU && IPW == 2) {
-        // two waves: fragment hq whole
-        *reinterpret_cast<bf16x8*>(u_out + 16 * 32 * hq) =
-            bf16x8{uw[0][0], uw[0][1], uw[0][2], uw[0][3], uw[1][0], uw[1][1], uw[1][2], uw[1][3]};
-      } else if constexpr (RSU) {
-        *reinterpret_cast<bf16x4*>(u_out + 16 * 32 * (I0 >> 1) + 4 * (I0 & 1)) = uw[0];
-      } else if constexpr (NH == 1) {
-        store_frag(u_out, uf[0]);
-        store_frag(u_out + 16 * 32, uf[1]);
-      } else if constexpr (NH == 2) {
-        store_frag(u_out + 16 * 32 * hq, hq == 0 ? uf[0] : uf[1]);
-      } else {
-        // four waves: one 8-byte half of one fragment each
-        const bf16x8 x = (hq >> 1) == 0 ? uf[0].v : uf[1].v;
-        const bf16x4 y = (hq & 1) == 0 ? bf16x4{x[0], x[1], x[2], x[3]} : bf16x4{x[4], x[5], x[6], x[7]};
-        *reinterpret_cast<bf16x4*>(u_out + 16 * 32 * (hq >> 1) + 4 * (hq & 1)) = y;
-      }
-    }
-  }
-
-  if (a.ST) {
-    wait_vm<0>();
-#pragma unroll
-    for (int tc = 0; tc < NCT; ++tc)
-      *reinterpret_cast<f32x4*>(a.ST + ((size_t)bh * a.dv + v) * DK + c0 + pair_feat(tc, g4)) = S[tc];
-  }
-}
-
 // Outputs of a group of consecutive chunks (eight waves).  Per chunk the
 // decayed, masked scores
 //   P_ij = e^{gamma_i - gamma_j} (q_i . k_j)  (j <= i)
@@ -1081,12 +600,7 @@ hipError_t run_tri(const TriArgs& a, hipStream_t st) {
   const int N = (a.T + kChunk - 1) / kChunk;
   const int nblk = a.B * a.H * N;
   if (nblk == 0) return hipSuccess;
-  if constexpr (sizeof(T) == 2 && DK >= 128)
-    if (a.W) {
-      hipLaunchKernelGGL((gdn_tri_kernel<T, DK, true>), dim3(nblk), dim3(kThreads), 0, st, a);
-      return hipGetLastError();
-    }
-  hipLaunchKernelGGL((gdn_tri_kernel<T, DK, false>), dim3(nblk), dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL((gdn_tri_kernel<T, DK>), dim3(nblk), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 template <typename T, int DK, int NPR, int NH>
@@ -1096,49 +610,16 @@ hipError_t run_gdn_state_v(const GdnArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((gdn_state_kernel<T, DK, NPR, NH>), dim3(nblk), dim3(64 * NPR * NH), 0, st, a);
   return hipGetLastError();
 }
-// Split the key features over as many waves (1, 2, 4 or 8, at least 32
-// features each) as it takes to give every SIMD of the chip a wave, with four
-// waves per workgroup where the split allows.
-// LDS of the streamed kernel with a ring of `ns` stages
-constexpr size_t gdn_dma_lds(int dk, int npr, int nh, int ns, bool rs, bool rsu) {
-  return (size_t)ns * (kChunk * dk * 2 + kChunk * kChunk * 2 + kChunk * 16 * npr * 2 + 4 * kChunk * 4) +
-         (nh > 1 ? (size_t)npr * nh * 4 * 64 * 16 : 16) + (rs ? (size_t)npr * 2 * 64 * 16 * (rsu ? 2 : 1) : 0);
-}
-// With a key split the exchange is the reduce-scatter form: bit-identical, and
-// measured on the 1.3B shape 380 -> 362 us per forward call at T = 4096 and
-// 915 -> 865 us at T = 20480.
-template <int DK, int NPR, int NH, bool RS = (NH > 1), bool RSU = (NH > 1)>
-hipError_t run_gdn_state_dma(const GdnArgs& a, hipStream_t st) {
-  const int nblk = a.B * a.H * (a.dv / (16 * NPR));
-  if (nblk == 0) return hipSuccess;
-  // three stages where they fit in the compute unit's 160 KB of LDS
-  constexpr int NS = gdn_dma_lds(DK, NPR, NH, 3, RS, RSU) <= 160 * 1024 ? 3 : 2;
-  hipLaunchKernelGGL((gdn_state_dma_kernel<DK, NPR, NH, NS, RS, RSU>), dim3(nblk), dim3(64 * NPR * NH), 0, st, a);
-  return hipGetLastError();
-}
+// Split the key features over as many waves (1, 2 or 4, at least 32 features
+// each) as it takes to give every SIMD of the chip a wave, with four waves per
+// workgroup.
 template <typename T, int DK>
 hipError_t run_gdn_state(const GdnArgs& a, hipStream_t st) {
   const long long slices = (long long)a.B * a.H * (a.dv / 16);
   constexpr int kSimds = 1024;
-  if constexpr (sizeof(T) == 2 && (DK == 128 || DK == 256)) {
-    // one workgroup per compute unit: at dk = 128, 64-wide value slices once
-    // there are enough of them, so that the chip takes every slice in one
-    // round (at dk = 256 that split would not fit the registers)
-    if constexpr (DK == 128)
-      if (slices >= kSimds && a.dv % 64 == 0) return run_gdn_state_dma<DK, 4, 2>(a, st);
-    if (slices * 2 >= kSimds && a.dv % 32 == 0) return run_gdn_state_dma<DK, 2, 4>(a, st);
-    // at most one value tile per compute unit at dk = 256 (long sequences of
-    // few heads): one tile per workgroup over four waves, which beats eight
-    // waves of the register-prefetch form (fewer partial products to exchange)
-    if constexpr (DK == 256)
-      if (slices <= kSimds / 4) return run_gdn_state_dma<DK, 1, 4>(a, st);
-  }
-  if (slices >= kSimds || DK < 64) return run_gdn_state_v<T, DK, 4, 1>(a, st);
+  if (slices >= kSimds) return run_gdn_state_v<T, DK, 4, 1>(a, st);
   if (slices * 2 >= kSimds || DK < 128) return run_gdn_state_v<T, DK, 2, 2>(a, st);
-  if constexpr (DK >= 128) {
-    if (slices * 4 >= kSimds || DK < 256) return run_gdn_state_v<T, DK, 1, 4>(a, st);
-  }
-  if constexpr (DK >= 256) return run_gdn_state_v<T, DK, 1, 8>(a, st);
+  if constexpr (DK >= 128) return run_gdn_state_v<T, DK, 1, 4>(a, st);
   return hipErrorInvalidValue;
 }
 template <typename T, int DK, int VPW, int IPW>
@@ -1220,8 +701,8 @@ hipError_t launch_gdn_state(const GdnArgs& a, bool is_bf16, hipStream_t st) {
   if (is_bf16) {
     switch (a.dk) {
       case 64: return run_gdn_state<bf16_t, 64>(a, st);
-      case 128: return run_gdn_state<bf16_t, 128>(a, st);
-      case 256: return run_gdn_state<bf16_t, 256>(a, st);
+      case 128:
+      case 256: return launch_gdn_state_roles(a, st);
     }
   } else {
     switch (a.dk) {

@@ -120,7 +120,6 @@ struct GlaOutArgs {
 
 // Gated DeltaNet chunk transform (chunk-parallel): Tm = (I + A)^{-1} and the
 // chunk's decay coefficients.
-constexpr int kTbBytes = 6 * 1024;  // Tb of a chunk (bf16)
 struct TriArgs {
   const void* k;         // [B,T,H,dk] io
   const float* logalpha; // [B,T,H]
@@ -135,11 +134,6 @@ struct TriArgs {
   // coefficients beta e^gamma and e^{gamma_C - gamma} that multiply key rows
   // in the state pass and the output kernel's carry are stored times rk
   const float* rk = nullptr;
-  // operands of the WY state pass (workspace; null: not formed, else Tm may be
-  // null), lane-native blocks of 64 lanes x 8 elements: Tb = Tm diag(beta)
-  // [B*H, N, kTbBytes], W = -Tm diag(beta e^gamma) K [B*H, N, dk / 8 blocks]
-  void* W = nullptr;
-  void* Tb = nullptr;
 };
 
 // Gated DeltaNet state recurrence (sequential over chunks): writes the
@@ -160,8 +154,6 @@ struct GdnArgs {
   int B, T, H, dk, dv;
   int sstride = 1;
   const int* cu = nullptr;  // as TriArgs
-  const void* W = nullptr;  // WY state pass: as TriArgs
-  const void* Tb = nullptr;
 };
 
 // Gated DeltaNet output, one workgroup per group of `group` chunks (the
@@ -383,9 +375,7 @@ inline GlaPlan gla_plan(long long bh, long long nc, int dk, int dv, bool is_bf16
 }
 hipError_t launch_gdn_tri(const TriArgs& a, bool is_bf16, hipStream_t st);
 hipError_t launch_gdn_state(const GdnArgs& a, bool is_bf16, hipStream_t st);
-// The WY form of the state pass (needs TriArgs.W and Tb) and where it is used.
-hipError_t launch_gdn_wy_state(const GdnArgs& a, hipStream_t st);
-bool gdn_wy(long long bh, long long nc, int dk, int dv, bool is_bf16, bool every_state);
+hipError_t launch_gdn_state_roles(const GdnArgs& a, hipStream_t st);  // bf16, dk = 128 or 256
 hipError_t launch_gdn_out(const GdnOutArgs& a, bool is_bf16, hipStream_t st);
 hipError_t launch_copy_or_zero(float* dst, const float* src, size_t n, hipStream_t st);
 

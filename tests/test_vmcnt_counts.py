@@ -1,12 +1,11 @@
-"""The streamed Gated DeltaNet state pass (gdn_state_dma_kernel) waits on the
-vector-memory counter with counts derived from its own constants: per chunk,
-NIW global_load_lds pieces of the chunk NSTAGE - 1 ahead, then NKH state stores
-(every sstride-th chunk) and NSU U^T stores; vmcnt(n) lets exactly those stay in
-flight.  The counts are only right if the compiler issues exactly those
-vector-memory instructions in the chunk loop and no others (a register spill, a
-split or merged load or an extra global load would shift them and the wait would
+"""The loader waves of the Gated DeltaNet state pass (gdn_state_roles_kernel) wait on
+the vector-memory counter with a count derived from the kernel's own constants:
+per chunk NL global_load_lds pieces, of which those of the next chunk may stay in
+flight.  The count is only right if the compiler issues exactly those loads in
+the loaders' chunk loop and no other vector-memory instruction (a register spill,
+a split or merged load or an extra global load would shift it and the wait would
 silently under-wait).  This test compiles the kernel source to gfx950 assembly
-with the library's own flags and checks the chunk loop of every instantiation
+with the library's own flags and checks the loaders' loop of every instantiation
 the library launches, on the CPU.
 """
 import os
@@ -21,28 +20,22 @@ from paper_2606_01294_amd import build as B
 C = 64
 
 
-def expected(DK, NPR, NH):
-    """(stream-load instructions in the loop, stores in the loop) from the kernel's
-    constants; a piece shared by several waves is one lane-masked load in each."""
-    NW, BVS = NPR * NH, 16 * NPR
-    DKH = DK // NH
-    NKH = DKH // 32
-    NIK, NIT, NIV = C * DK * 2 // 1024, C * C * 2 // 1024, C * BVS * 2 // 1024
-    NIVW = (NIV + NW - 1) // NW
-    NIW = NIK // NW + NIT // NW + NIVW + 1
-    NSU = 2 if NH == 1 else 1
-    return NIW, NKH + NSU
+def expected(DK, NPR):
+    """Loads of one loader wave and chunk: K, Tm, the V slice and the coefficients; a piece shared by
+    several waves is one lane-masked load in each."""
+    pieces = [C * DK * 2 // 1024, C * C * 2 // 1024, C * 16 * NPR * 2 // 1024]
+    return sum((n + 3) // 4 for n in pieces) + 1
 
 
-# the instantiations the library launches (template <DK, NPR, NH, NSTAGE, RS, RSU>)
-INSTANCES = [(256, 2, 4, 2, 1, 1), (256, 1, 4, 3, 1, 1), (128, 4, 2, 3, 1, 1), (128, 2, 4, 3, 1, 1)]
+# the instantiations the library launches (template <DK, NPR, NG>)
+INSTANCES = [(128, 1, 4), (128, 2, 4), (128, 4, 4), (128, 4, 2), (256, 1, 4), (256, 2, 4)]
 
 
 @pytest.fixture(scope="module")
-def gdn_asm():
-    src = os.path.join(B.CSRC, "ccq_gdn.hip")
+def roles_asm():
+    src = os.path.join(B.CSRC, "ccq_gdn_roles.hip")
     with tempfile.TemporaryDirectory() as d:
-        out = os.path.join(d, "ccq_gdn.s")
+        out = os.path.join(d, "roles.s")
         cmd = [B._hipcc()] + B.COMMON + B.DEVICE + ["--cuda-device-only", "-S", src, "-o", out]
         res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:
@@ -50,31 +43,24 @@ def gdn_asm():
         return open(out).read()
 
 
-def chunk_loop(asm, sym):
-    """Instructions of the kernel's outermost loop (the chunk loop): from the loop
-    header label to the last branch back to it."""
-    body = asm.split("\n" + sym + ":", 1)[1].split("s_endpgm", 1)[0].split("\n")
-    head = [i for i, line in enumerate(body) if "Loop Header: Depth=1" in line]
-    assert len(head) == 1, "one chunk loop expected in %s" % sym
-    label = body[head[0]].split(":", 1)[0].strip()
-    back = [i for i, line in enumerate(body) if re.search(r"s_cbranch\w*\s+" + re.escape(label) + r"\b", line)
-            or re.search(r"s_branch\s+" + re.escape(label) + r"\b", line)]
-    assert back, "no branch back to %s" % label
-    return [line.split(";")[0].strip() for line in body[head[0]:max(back) + 1]]
-
-
-@pytest.mark.parametrize("inst", INSTANCES, ids=lambda t: "dk%d-npr%d-nh%d-ns%d-rs%d-rsu%d" % t)
-def test_state_pass_loop_issues_the_counted_vector_memory_ops(gdn_asm, inst):
-    DK, NPR, NH, NS, RS, RSU = inst
-    sym = "_ZN3ccq20gdn_state_dma_kernelILi%dELi%dELi%dELi%dELb%dELb%dEEEvNS_7GdnArgsE" % inst
-    assert ("\n" + sym + ":") in gdn_asm, "instantiation %s not emitted" % sym
-    loop = chunk_loop(gdn_asm, sym)
-    mnem = [line.split()[0] for line in loop if line and not line.startswith((".", ";"))]
-    vmem = [m for m in mnem if m.startswith(("global_", "buffer_", "scratch_", "flat_"))]
-    loads = [m for m in vmem if m == "global_load_lds_dwordx4"]
-    stores = [m for m in vmem if m.startswith("global_store_")]
-    other = [m for m in vmem if m not in ("global_load_lds_dwordx4",) and not m.startswith("global_store_")]
-    n_loads, n_stores = expected(DK, NPR, NH)
-    assert not other, "unexpected vector-memory instructions in the chunk loop: %s" % other
-    assert len(loads) == n_loads, (len(loads), n_loads)
-    assert len(stores) == n_stores, (len(stores), n_stores)
+@pytest.mark.parametrize("inst", INSTANCES, ids=lambda t: "dk%d-npr%d-ng%d" % t)
+def test_state_pass_loop_issues_the_counted_vector_memory_ops(roles_asm, inst):
+    sym = "_ZN3ccq22gdn_state_roles_kernelILi%dELi%dELi%dEEEvNS_7GdnArgsE" % inst
+    assert ("\n" + sym + ":") in roles_asm, "instantiation %s not emitted" % sym
+    body = roles_asm.split("\n" + sym + ":", 1)[1].split(".Lfunc_end", 1)[0].split("\n")
+    assert not any(x.strip().startswith(("scratch_", "buffer_")) for x in body), "registers spilled"
+    label = {m.group(1): i for i, x in enumerate(body) for m in [re.match(r"(\.LBB\d+_\d+):", x)] if m}
+    loops = {}
+    for i, x in enumerate(body):
+        m = re.search(r"s_c?branch\w*\s+(\.LBB\d+_\d+)", x)
+        if m and label[m.group(1)] <= i:
+            loops[label[m.group(1)]] = max(i, loops.get(label[m.group(1)], 0))
+    counts = []
+    for h, e in loops.items():
+        ins = [x.split(";")[0].split() for x in body[h:e + 1]]
+        ins = [x[0] for x in ins if x and not x[0].startswith(".")]
+        if not any("mfma" in x for x in ins):  # the loaders' loop
+            vm = [x for x in ins if x.startswith(("global_", "buffer_", "scratch_", "flat_"))]
+            counts.append((vm.count("global_load_lds_dwordx4"), len(vm)))
+    n = expected(*inst[:2])
+    assert (n, n) in counts, (n, counts)
