@@ -37,22 +37,19 @@ CHUNK = 64
 
 
 def gla_seg(bh: int, nc: int, dk: int, dv: int) -> int:
-    """Chunks per segment of the GLA state pass (the library's policy gla_plan for bf16 io and gates; 0 =
-    one segment): segment count and value columns per workgroup (64 or 128) that minimise
-    rounds of 512 workgroups x chunks per segment x step cost plus the scan."""
-    best, best_cost = 0, None
-    for vs in (64, 128) if dv % 128 == 0 else (64,):
-        tiles = bh * (dk // 64) * (dv // vs)
-        for ns in range(1, min(64, nc) + 1):
-            sl = -(-nc // ns)
-            if -(-nc // sl) != ns or (ns > 1 and sl < 4) or (ns == 1 and vs > 64):
-                continue
-            cost = -(-(tiles * ns) // 512) * sl * (10 if vs == 64 else 14)
-            if ns > 1:
-                cost += 15 + bh * ns * dk * dv // 62900
-            if best_cost is None or cost < best_cost:
-                best, best_cost = (sl if ns > 1 else 0), cost
-    return best
+    """Chunks per segment of the GLA state pass (the library's policy; 0 = one
+    segment): the segment count minimising rounds of 512 workgroups x chunks per
+    segment (+2 for the scan when segmented), the fewest segments on a tie."""
+    tiles = bh * (dk // 64) * (dv // 64)
+    best_ns, best_cost = 1, None
+    for ns in range(1, min(64, nc) + 1):
+        sl = -(-nc // ns)
+        if -(-nc // sl) != ns or (ns > 1 and sl < 4):
+            continue
+        cost = -(-(tiles * ns) // 512) * sl + (2 if ns > 1 else 0)
+        if best_cost is None or cost < best_cost:
+            best_ns, best_cost = ns, cost
+    return -(-nc // best_ns) if best_ns > 1 else 0
 
 
 def clean_seg(bh: int, nc: int) -> int:

@@ -125,7 +125,7 @@ hipError_t run_clean_stats(const ccq::CleanArgs& a, bool bf, hipStream_t st) {
 struct FwdLayout {
   size_t qclean = 0, states = 0, Tm = 0, gam = 0, U = 0, total = 0;
   size_t segsum = 0, segdec = 0, cdec = 0, entries = 0;  // GLA state pass in segments
-  int gla_seg = 0, gla_vs = 64;
+  int gla_seg = 0;
   CleanWs clean;
 };
 
@@ -143,10 +143,7 @@ FwdLayout fwd_layout(const ccq_shape* s, ccq_backbone bb) {
   L.clean = take_clean_ws(s, take);
   if (bb == CCQ_GLA) {
     const long long nc = (s->T + 63) / 64;
-    const ccq::GlaPlan plan = ccq::gla_plan((long long)s->B * s->H, nc, s->dk, s->dv, s->io_dtype == CCQ_BF16,
-                                            s->gate_dtype == CCQ_BF16);
-    L.gla_seg = plan.seg;
-    L.gla_vs = plan.vs;
+    L.gla_seg = ccq::gla_seg((long long)s->B * s->H, nc, s->dk, s->dv);
     if (L.gla_seg > 0) {
       const size_t bh = (size_t)s->B * s->H, ns = (nc + L.gla_seg - 1) / L.gla_seg;
       L.segsum = take(bh * ns * s->dv * s->dk * sizeof(float));
@@ -329,7 +326,6 @@ ccq_status run_forward(ccq_backbone bb, const ccq_shape* s, const void* q, const
     sa.group = ccq::gla_out_group(s->B, s->H, s->T, s->dk, s->dv, bf);  // one state per output group
     if (L.gla_seg > 0) {
       sa.seg = L.gla_seg;
-      sa.vs = L.gla_vs;
       sa.ST = nullptr;
       sa.segsum = reinterpret_cast<float*>(ws + L.segsum);
       sa.segdec = reinterpret_cast<float*>(ws + L.segdec);

@@ -36,11 +36,8 @@ namespace ccq {
 // chunks from last to first it carries the state adjoint D = dL/dS_{r+1} and
 // stores it for every chunk, with  D^T <- diag(e^{b_C}) D^T + s (Q e^{b})^T dO
 // (a.k = q_clean, a.v = dO, a.states = the adjoints, a.scale = s).
-// (The register bound of two waves per SIMD keeps two workgroups of 128 columns
-// on a compute unit: 42.7 -> 31.5 us at 32 heads of 32 chunks; without it the
-// compiler takes 312 registers.)
 template <typename T, typename TG, int NVT, bool kRev = false>
-__global__ __launch_bounds__(kThreads, NVT >= 8 ? 2 : 1) void gla_state_kernel(const GlaStateArgs a) {
+__global__ __launch_bounds__(kThreads, 1) void gla_state_kernel(const GlaStateArgs a) {
   constexpr int C = kChunk, BK = 64, VB = 16 * NVT;
   constexpr int P = Pad<T>::value, PG = Pad<TG>::value;
   constexpr int LDK = BK + P, LDG = BK + PG, LDV = VB + P;
@@ -592,12 +589,9 @@ hipError_t run_gla_state_v(const GlaStateArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((gla_state_kernel<T, TG, NVT, kRev>), dim3(nblk), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
-// 64-wide value slices when they still give every SIMD a wave, else 32 or 16;
-// 128-wide ones where gla_plan cut the sequence for them.
+// 64-wide value slices when they still give every SIMD a wave, else 32 or 16.
 template <typename T, typename TG, bool kRev = false>
 hipError_t run_gla_state(const GlaStateArgs& a, hipStream_t st) {
-  if constexpr (sizeof(T) == 2 && sizeof(TG) == 2 && !kRev)
-    if (a.seg > 0 && a.vs == 128) return run_gla_state_v<T, TG, 8, kRev>(a, st);
   const long long waves64 = (long long)a.B * a.H * (a.dk / 64) * (a.dv / 64) * 4 * gla_nseg(a);
   if (waves64 >= 1024) return run_gla_state_v<T, TG, 4, kRev>(a, st);
   if (waves64 * 2 >= 1024) return run_gla_state_v<T, TG, 2, kRev>(a, st);

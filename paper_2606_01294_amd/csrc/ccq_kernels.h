@@ -80,7 +80,6 @@ struct GlaStateArgs {
   void* states;       // [B*H, N, dv, dk] io: chunk-entry local states
   int B, T, H, dk, dv;
   int seg;            // chunks per segment, 0 = all
-  int vs = 64;        // value columns per workgroup with segments (gla_plan)
   float* segsum;      // [B*H, NS, dv, dk] fp32: local state at each segment's end (NS > 1)
   float* segdec;      // [B*H, NS, dk] fp32: e^{sum of the segment's log decays}
   float* cdec;        // [B*H, N, dk] fp32: e^{log decays of the segment before each chunk}
@@ -336,42 +335,31 @@ inline int clean_seg(long long bh, long long nc) {
 hipError_t launch_gla_state(const GlaStateArgs& a, bool is_bf16, bool gate_bf16, hipStream_t st);
 hipError_t launch_gla_out(const GlaOutArgs& a, bool is_bf16, bool gate_bf16, hipStream_t st);
 hipError_t launch_gla_scan(const GlaScanArgs& a, bool is_bf16, hipStream_t st);
-// The GLA forward state pass: chunks per segment (0: one segment) and value
-// columns per workgroup, for bh heads of nc chunks.  A workgroup carries a 64 x
-// vs tile of S through its segment's chunks, two workgroups per compute unit;
-// the segments then meet in a scan.  Every value slice of a head forms the
-// chunk's decayed keys again (about two thirds of a 64-wide step's instructions),
-// so wide slices and shorter segments do the same work in fewer instructions.
-// The plan minimises rounds of 512 workgroups x chunks per segment x the cost of
-// a chunk step (64 columns 10, 128 columns 14: a tenth is about 0.19 us), plus,
-// with more than one segment (of at least 4 chunks), the scan: 15 and the bytes
-// of the segment totals and entry states (12 per element, at 4 TB/s); the fewest
-// segments on a tie.  State pass and scan together, 64 columns only against the
-// plan: 32 heads of 32 chunks, dk = 128, dv = 256: 44 -> 38 us; 4 heads of 320: 52
-// -> 43 us.  32-bit gates keep to 64 columns: a 128-wide workgroup's LDS (94 KB)
-// would be alone on its compute unit (whole forward, 32 heads of 64 chunks: 198 us
-// with 64 columns, 202 with 128).
-struct GlaPlan {
-  int seg, vs;
-};
-inline GlaPlan gla_plan(long long bh, long long nc, int dk, int dv, bool is_bf16, bool gate_bf16) {
-  GlaPlan best{0, 64};
-  long long best_cost = -1;
-  for (int vs = 64; vs <= (is_bf16 && gate_bf16 && dv % 128 == 0 ? 128 : 64); vs *= 2) {
-    const long long tiles = bh * (dk / 64) * (dv / vs);
-    for (long long ns = 1; ns <= 64 && ns <= nc; ++ns) {
-      const long long sl = (nc + ns - 1) / ns;
-      if ((nc + sl - 1) / sl != ns || (ns > 1 && sl < 4)) continue;  // ns segments of sl >= 4 chunks
-      if (ns == 1 && vs > 64) continue;
-      const long long cost = ((tiles * ns + 511) / 512) * sl * (vs == 64 ? 10 : 14) +
-                             (ns > 1 ? 15 + bh * ns * dk * dv / 62900 : 0);
-      if (best_cost < 0 || cost < best_cost) {
-        best_cost = cost;
-        best = GlaPlan{ns > 1 ? (int)sl : 0, vs};
-      }
+// Chunks per segment of the GLA state pass (0: one segment) for bh heads of
+// nc chunks.  A workgroup carries one 64 x (16 NVT) tile of S through its
+// segment's chunks, two workgroups per compute unit; the segments then meet
+// in a scan.  The segment count minimises rounds of 512 workgroups x chunks
+// per segment, plus two chunk steps for the scan when there is more than one
+// segment (of at least 4 chunks); the fewest segments on a tie.  Every segment
+// after the first adds a rounding to bf16 to the states that the outputs read (a
+// local part and an entry instead of their sum), so the count is not raised for
+// speed alone: 128 value columns a workgroup and twice the segments took 111
+// instead of 114 us a call at 32 heads of 32 chunks and 142 instead of 148 at 4
+// heads of 320, and put o 4.01e-3 instead of 4.00e-3 from the exact result at the
+// former; 64 heads of 28 chunks went from one segment to two.
+inline int gla_seg(long long bh, long long nc, int dk, int dv) {
+  const long long tiles = bh * (dk / 64) * (dv / 64);
+  long long best_ns = 1, best_cost = -1;
+  for (long long ns = 1; ns <= 64 && ns <= nc; ++ns) {
+    const long long sl = (nc + ns - 1) / ns;
+    if ((nc + sl - 1) / sl != ns || (ns > 1 && sl < 4)) continue;  // ns segments of sl >= 4 chunks
+    const long long cost = ((tiles * ns + 511) / 512) * sl + (ns > 1 ? 2 : 0);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best_ns = ns;
     }
   }
-  return best;
+  return best_ns > 1 ? (int)((nc + best_ns - 1) / best_ns) : 0;
 }
 hipError_t launch_gdn_tri(const TriArgs& a, bool is_bf16, hipStream_t st);
 hipError_t launch_gdn_state(const GdnArgs& a, bool is_bf16, hipStream_t st);
