@@ -512,7 +512,7 @@ def ccq_decode(q, k, v, gate, lam, S, C, mu, t0, backbone=CCQ_GLA, beta=None, sc
         need = ccq_decode_workspace_size(shape)
         if need:
             workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    rc = lib().ccq_decode(shape, int(backbone), q.data_ptr(), _p(k), v.data_ptr(), gate.data_ptr(),
+    rc = lib().ccq_decode(shape, int(backbone), q.data_ptr(), _p(k), v.data_ptr(), _p(gate),
                           _p(beta), _p(lam), S.data_ptr(), C.data_ptr(), mu.data_ptr(),
                           o.data_ptr(), _p(workspace),
                           0 if workspace is None else workspace.numel(), _stream(stream))

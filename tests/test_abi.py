@@ -195,6 +195,25 @@ def test_decode_entry_point_validation():
     assert call_decode(shape(B=0, T=1), ptr=0, ws_ptr=None) == 0
 
 
+@pytest.mark.parametrize("missing", ["k", "logalpha", "lam"])
+def test_decode_binding_passes_a_missing_tensor_to_the_library(missing):
+    """A tensor that is not given is refused by the library's own check (stream given: the binding
+    asks for torch's current one otherwise)."""
+    import types
+
+    import torch
+    B, H, dk = 2, 3, 64
+
+    def z(*s):
+        return torch.zeros(s)
+    t = dict(k=z(B, H, dk), logalpha=z(B, H), lam=z(B, H))
+    t[missing] = None
+    with pytest.raises(ccq.CcqError, match="ccq_decode"):
+        ccq.ccq_decode(z(B, H, dk), t["k"], z(B, H, dk), t["logalpha"], t["lam"], z(B, H, dk, dk), z(B, H, dk, dk),
+                       z(B, H, dk), 5, backbone=ccq.CCQ_GDN, beta=z(B, H),
+                       stream=types.SimpleNamespace(cuda_stream=0))
+
+
 def test_prep_entry_point_validation():
     P = ctypes.c_void_p
 
