@@ -199,6 +199,7 @@ def _fwd(backbone, q, k, v, gate, lam, beta, S0, C0, mu0, scale, centered, t0, c
     gate_dtype = gate.dtype if backbone == CCQ_GLA else q.dtype
     shape = make_shape(B, T, H, dk, dv, q.dtype, gate_dtype, scale, centered, t0, chunk,
                        decay_aligned)
+    _check(q, "q", q.shape, q.dtype, dev)
     _check(k, "k", (B, T, H, dk), q.dtype, dev)
     _check(v, "v", (B, T, H, dv), q.dtype, dev)
     if backbone == CCQ_GLA:
@@ -271,6 +272,7 @@ def ccq_gdn_fwd_noalloc(q, k, v, logalpha, beta, lam, S0=None, C0=None, mu0=None
     dv = v.shape[-1]
     dev = q.device
     shape = make_shape(B, T, H, dk, dv, q.dtype, q.dtype, scale, centered, t0, chunk)
+    _check(q, "q", q.shape, q.dtype, dev)
     _check(k, "k", (B, T, H, dk), q.dtype, dev)
     _check(v, "v", (B, T, H, dv), q.dtype, dev)
     _check(logalpha, "logalpha", (B, T, H), torch.float32, dev)
@@ -318,6 +320,7 @@ def ccq_fwd_bwd(q, k, v, g, lam, dO, scale=1.0, centered=True, chunk=64, out=Non
             raise ValueError("beta is required for the Gated DeltaNet training step")
         _check(g, "logalpha", (B, T, H), torch.float32, dev)
         _check(beta, "beta", (B, T, H), torch.float32, dev)
+    _check(q, "q", q.shape, q.dtype, dev)
     _check(k, "k", (B, T, H, dk), q.dtype, dev)
     _check(v, "v", (B, T, H, dv), q.dtype, dev)
     _check(dO, "dO", (B, T, H, dv), q.dtype, dev)
@@ -375,6 +378,7 @@ def _varlen_fwd(backbone, q, k, v, gate, beta, lam, cu_seqlens, max_len, S0, C0,
     shape = _varlen_shape(backbone, q, v, gate, cu_seqlens, max_len, scale, centered, t0,
                           decay_aligned)
     B = shape.B
+    _check(q, "q", q.shape, q.dtype, dev)
     _check(k, "k", (rows, H, dk), q.dtype, dev)
     _check(v, "v", (rows, H, dv), q.dtype, dev)
     if backbone == CCQ_GLA:
@@ -449,6 +453,7 @@ def ccq_fwd_bwd_varlen(q, k, v, g, lam, dO, cu_seqlens, max_len, scale=1.0, cent
             raise ValueError("beta is required for the Gated DeltaNet training step")
         _check(g, "logalpha", (rows, H), torch.float32, dev)
         _check(beta, "beta", (rows, H), torch.float32, dev)
+    _check(q, "q", q.shape, q.dtype, dev)
     _check(k, "k", (rows, H, dk), q.dtype, dev)
     _check(v, "v", (rows, H, dv), q.dtype, dev)
     _check(dO, "dO", (rows, H, dv), q.dtype, dev)
@@ -499,7 +504,8 @@ def ccq_decode(q, k, v, gate, lam, S, C, mu, t0, backbone=CCQ_GLA, beta=None, sc
         args = ((gate, "g", key, gate.dtype),)
     else:
         args = ((gate, "logalpha", tok, f32), (beta, "beta", tok, f32))
-    for t, name, shp, d in ((k, "k", key, dt), (v, "v", val, dt), (lam, "lam", tok, f32)) + args + (
+    for t, name, shp, d in ((q, "q", key, dt), (k, "k", key, dt), (v, "v", val, dt),
+                            (lam, "lam", tok, f32)) + args + (
             (S, "S", (B, H, dv, dk), f32), (C, "C", (B, H, dk, dk), f32), (mu, "mu", key, f32)):
         if t is None or t.shape != shp or t.dtype != d or t.device != dev or not t.is_contiguous():
             _check(t, name, shp, d, dev)
@@ -530,6 +536,7 @@ def ccq_prep(q_raw, k_raw, w_lam, b_lam, out=None, stream=None):
     out=dict(q=q_raw, k=k_raw) to normalise in place."""
     B, T, H, dk = q_raw.shape
     dev = q_raw.device
+    _check(q_raw, "q_raw", q_raw.shape, q_raw.dtype, dev)
     _check(k_raw, "k_raw", (B, T, H, dk), q_raw.dtype, dev)
     _check(w_lam, "w_lam", (H, H * dk), torch.float32, dev)
     _check(b_lam, "b_lam", (H,), torch.float32, dev)
@@ -562,6 +569,7 @@ def ccq_fwd_raw(q_raw, k_raw, w_lam, b_lam, v, gate, beta=None, backbone=CCQ_GLA
     dev = q_raw.device
     gate_dtype = gate.dtype if backbone == CCQ_GLA else q_raw.dtype
     shape = make_shape(B, T, H, dk, dv, q_raw.dtype, gate_dtype, scale, centered, t0, chunk)
+    _check(q_raw, "q_raw", q_raw.shape, q_raw.dtype, dev)
     _check(k_raw, "k_raw", (B, T, H, dk), q_raw.dtype, dev)
     _check(v, "v", (B, T, H, dv), q_raw.dtype, dev)
     _check(w_lam, "w_lam", (H, H * dk), torch.float32, dev)

@@ -214,6 +214,39 @@ def test_decode_binding_passes_a_missing_tensor_to_the_library(missing):
                        stream=types.SimpleNamespace(cuda_stream=0))
 
 
+def test_binding_refuses_a_strided_query():
+    """The kernels read q through the sizes alone: a strided q is refused like every other strided
+    input, by every entry point."""
+    import torch
+    B, T, H, dk = 2, 3, 4, 64
+
+    def z(*s, **kw):
+        return torch.zeros(s, **kw)
+
+    def half(*s):
+        return z(*s[:-1], 2 * s[-1])[..., :s[-1]]
+    x, tok = z(B, T, H, dk), z(B, T, H)
+    q, p, cu = half(B, T, H, dk), half(T, H, dk), z(2, dtype=torch.int32)
+    y, ptok, w, b = z(T, H, dk), z(T, H), z(H, H * dk), z(H)
+    S, m = z(B, H, dk, dk), z(B, H, dk)
+    calls = {
+        "gla_fwd": lambda: ccq.ccq_gla_fwd(q, x, x, x, tok),
+        "gdn_fwd": lambda: ccq.ccq_gdn_fwd(q, x, x, tok, tok, tok),
+        "gdn_fwd_noalloc": lambda: ccq.ccq_gdn_fwd_noalloc(q, x, x, tok, tok, tok),
+        "fwd_bwd": lambda: ccq.ccq_fwd_bwd(q, x, x, x, tok, x),
+        "gla_fwd_varlen": lambda: ccq.ccq_gla_fwd_varlen(p, y, y, y, ptok, cu, T),
+        "gdn_fwd_varlen": lambda: ccq.ccq_gdn_fwd_varlen(p, y, y, ptok, ptok, ptok, cu, T),
+        "fwd_bwd_varlen": lambda: ccq.ccq_fwd_bwd_varlen(p, y, y, y, ptok, y, cu, T),
+        "decode": lambda: ccq.ccq_decode(half(B, H, dk), m, m, m, z(B, H), S, S, m, 5),
+        "prep": lambda: ccq.ccq_prep(q, x, w, b),
+        "fwd_raw": lambda: ccq.ccq_fwd_raw(q, x, w, b, x, x),
+    }
+    for name, call in calls.items():
+        with pytest.raises(ValueError, match="q.* must be contiguous"):
+            call()
+            pytest.fail(name)
+
+
 def test_prep_entry_point_validation():
     P = ctypes.c_void_p
 
