@@ -257,7 +257,9 @@ ccq_status ccq_gdn_fwd_varlen(const ccq_shape* s, const int32_t* cu_seqlens, con
                               const float* beta, const float* lam, const float* S0,
                               const float* C0, const float* mu0, void* o, float* ST, float* CT,
                               float* muT, void* workspace, size_t ws_bytes, void* stream);
-/* Training step on a packed batch (as ccq_fwd_bwd, t0 = 0). */
+/* Training step on a packed batch (as ccq_fwd_bwd, t0 = 0; as there, the
+ * outputs may not overlap the inputs, which are read after outputs are
+ * written). */
 ccq_status ccq_fwd_bwd_varlen(const ccq_shape* s, ccq_backbone bb, const int32_t* cu_seqlens,
                               const void* q, const void* k, const void* v,
                               const void* g_or_logalpha, const float* beta, const float* lam,

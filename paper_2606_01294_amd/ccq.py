@@ -438,10 +438,29 @@ def ccq_gdn_fwd_varlen(q, k, v, logalpha, beta, lam, cu_seqlens, max_len, S0=Non
                        scale, centered, t0, want_states, out, workspace, stream, decay_aligned)
 
 
+def _apart(stream, outs, *inputs):
+    """The inputs, those that share memory with one of `outs` as copies (made on the stream
+    of the call): the kernels read inputs after they have written outputs."""
+    spans = [(o.data_ptr(), o.data_ptr() + o.numel() * o.element_size())
+             for o in outs.values() if o is not None]
+
+    def one(t):
+        if t is None:
+            return None
+        a = t.data_ptr()
+        b = a + t.numel() * t.element_size()
+        if not any(a < end and begin < b for begin, end in spans):
+            return t
+        with torch.cuda.stream(stream):
+            return t.clone()
+    return [one(t) for t in inputs]
+
+
 def ccq_fwd_bwd_varlen(q, k, v, g, lam, dO, cu_seqlens, max_len, scale=1.0, centered=True,
                        out=None, workspace=None, stream=None, backbone=CCQ_GLA, beta=None):
     """Training step on a packed batch (layout as ccq_gla_fwd_varlen; dO [rows,H,dv]).
-    Returns the same dict as ccq_fwd_bwd, packed."""
+    Returns the same dict as ccq_fwd_bwd, packed.  Tensors given in `out` may be inputs
+    (out=dict(dq=q, ...): those inputs are copied first)."""
     rows, H, dk = q.shape
     dv = v.shape[-1]
     dev = q.device
@@ -458,6 +477,8 @@ def ccq_fwd_bwd_varlen(q, k, v, g, lam, dO, cu_seqlens, max_len, scale=1.0, cent
     _check(v, "v", (rows, H, dv), q.dtype, dev)
     _check(dO, "dO", (rows, H, dv), q.dtype, dev)
     _check(lam, "lam", (rows, H), torch.float32, dev)
+    if out:
+        q, k, v, g, beta, lam, dO = _apart(stream, out, q, k, v, g, beta, lam, dO)
     out = dict(out or {})
     out.setdefault("o", torch.empty((rows, H, dv), dtype=q.dtype, device=dev))
     out.setdefault("dq", torch.empty((rows, H, dk), dtype=q.dtype, device=dev))

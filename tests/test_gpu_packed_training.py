@@ -22,6 +22,34 @@ CASES = [(GLA, BF16, [300, 0, 64, 129, 1], 2, 128, 256, 337), (GLA, F32, [65, 19
          (GLA, BF16, [200, 150, 220], 2, 64, 128, 130), (GDN, BF16, [400, 70, 333], 1, 128, 64, 100)]
 
 
+@pytest.mark.parametrize("backbone", [GLA, GDN])
+@pytest.mark.parametrize("side", [False, True])
+def test_outputs_may_take_the_place_of_inputs(backbone, side):
+    """Every gradient over the input it belongs to, o over dO: the same results as into new tensors,
+    on the current stream and on another one."""
+    print("packed training in place", backbone, side, flush=True)
+    lens, H, dk, dv = [300, 64, 0, 450], 2, 128, 256
+    d = make_inputs(backbone, len(lens), max(lens), H, dk, dv, BF16, seed=3, keys="aniso", lam="random", with_dO=True)
+    g = {n: torch.cat([x[b, :L] for b, L in enumerate(lens)], dim=0).contiguous().cuda() for n, x in d.items()}
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).cuda()
+    gate = "g" if backbone == GLA else "logalpha"
+
+    def step(t, **kw):
+        return ccq.ccq_fwd_bwd_varlen(t["q"], t["k"], t["v"], t[gate], t["lam"], t["dO"], cu, max(lens),
+                                      backbone=backbone, beta=t.get("beta"), **kw)
+    want = step(g)
+    t = {n: x.clone() for n, x in g.items()}
+    out = dict(o=t["dO"], dq=t["q"], dk=t["k"], dv=t["v"], dg=t[gate], dlam=t["lam"])
+    if backbone == GDN:
+        out["dbeta"] = t["beta"]
+    torch.cuda.synchronize()
+    got = step(t, out=out, stream=torch.cuda.Stream() if side else None)
+    torch.cuda.synchronize()
+    for n in want:
+        assert got[n].data_ptr() == out[n].data_ptr()
+        assert torch.equal(got[n], want[n]), n
+
+
 @pytest.mark.parametrize("backbone,dtype,lens,H,dk,dv,bound", CASES)
 def test_packed_training_matches_oracle(backbone, dtype, lens, H, dk, dv, bound):
     print("packed training", backbone, dtype, lens, H, dk, dv, bound, flush=True)
