@@ -625,11 +625,7 @@ hipError_t scratch_on_current_device(void** out) {
 extern "C" {
 
 size_t ccq_varlen_workspace_size(const ccq_shape* s, ccq_backbone bb, int with_bwd) {
-  if (check_shape(s, bb) != CCQ_OK) return 0;
-  if (with_bwd && !ccq::bwd_supported(s->dk, s->dv, s->io_dtype == CCQ_BF16, bb == CCQ_GDN)) return 0;
-  // every kernel reads the packed rows directly; the training step's size stays
-  // above the padded call's, as it was when it held padded copies
-  return ccq_workspace_size(s, bb, with_bwd) + (with_bwd ? kAlign : 0);
+  return ccq_workspace_size(s, bb, with_bwd);  // every kernel reads the packed rows directly
 }
 
 ccq_status ccq_gla_fwd_varlen(const ccq_shape* s, const int32_t* cu_seqlens, const void* q, const void* k,
