@@ -549,7 +549,7 @@ ccq_status run_fwd_bwd(const ccq_shape* s, ccq_backbone bb, const int32_t* cu, c
 ccq_status check_varlen(const ccq_shape* s, ccq_backbone bb, const int32_t* cu) {
   ccq_status rc = check_shape(s, bb);
   if (rc != CCQ_OK) return rc;
-  if (s->B > 65535) return CCQ_ERR_UNSUPPORTED;  // one grid row per sequence
+  if (s->B > 65535) return CCQ_ERR_UNSUPPORTED;  // the documented limit
   if (s->B > 0 && (!cu || (reinterpret_cast<uintptr_t>(cu) & 3u))) return CCQ_ERR_INVALID_ARG;
   return CCQ_OK;
 }

@@ -374,11 +374,6 @@ __device__ __forceinline__ int xcd_logical_block(int x, int nblocks) {
   return (x % 8) * (nblocks / 8) + x / 8;
 }
 
-// Row offset of token (b, t, h) in a [B, T, H, D] tensor, in elements.
-__device__ __forceinline__ size_t tok_off(int b, int t, int h, int T, int H, int D) {
-  return (((size_t)b * T + t) * H + h) * (size_t)D;
-}
-
 // One 64-row chunk of a [*, D] token tensor held in registers as vectors of 8
 // elements (16 bytes for bf16, 32 for fp32), so tiles of either dtype share
 // one lane -> element mapping: lane l of every wave owns row l, wave w owns
@@ -419,15 +414,6 @@ struct ChunkTile {
   __device__ __forceinline__ void store(T* dst, int ld) const {
 #pragma unroll
     for (int u = 0; u < NV; ++u) *reinterpret_cast<vec_t*>(dst + row() * ld + col(u)) = get(u);
-  }
-  template <typename U>
-  __device__ __forceinline__ void store_t(U* dstT, int ldT) const {
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const vec_t x = get(u);
-#pragma unroll
-      for (int e = 0; e < VE; ++e) dstT[(col(u) + e) * ldT + row()] = static_cast<U>(static_cast<float>(x[e]));
-    }
   }
   // fp32 copy, row-major; an odd pitch keeps it conflict-free for lane = row
   __device__ __forceinline__ void store_f32(float* dst, int ld) const {
@@ -697,18 +683,6 @@ __device__ __forceinline__ int frag_tr_pair_lane_off(int l, int ld) {
   const int g = l >> 4, j = l & 15;
   if constexpr (sizeof(T) == 2) return (8 * g + (j >> 2)) * ld + 8 * (j & 3);
   else return 8 * g * ld + 8 * (j >> 2) + (j & 3);
-}
-
-// Chunks of sequence b that hold tokens.  Without offsets, all N chunks of the
-// [B, T] batch; with the offsets cu of a packed batch laid out padded (rows
-// past each sequence's end zero), ceil(len_b / 64) with len_b = cu[b+1] - cu[b]
-// clamped to [0, T]: the chunks past them hold only zero rows, which leave
-// every state unchanged, so the state and output passes may skip them.
-__device__ __forceinline__ int live_chunks(const int* cu, int b, int T, int N) {
-  if (!cu) return N;
-  int len = cu[b + 1] - cu[b];
-  len = len < 0 ? 0 : (len > T ? T : len);
-  return (len + kChunk - 1) / kChunk;
 }
 
 // Sequence b of a batch: its first row in the token tensors and its length.

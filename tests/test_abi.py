@@ -275,7 +275,7 @@ def test_varlen_entry_point_validation():
                                             P(ptr), None, None, None, P(FAKE), ws_bytes, None)
     assert call(shape(), cu=None) == 1                      # offsets required
     assert call(shape(), cu=FAKE + 2) == 1                  # misaligned offsets
-    assert call(shape(B=70000)) == 2                        # one grid row per sequence
+    assert call(shape(B=70000)) == 2                        # the documented limit
     assert call(shape(dk=96)) == 2
     assert call(shape(), ptr=FAKE + 4) == 1
     assert call(shape(), ws_bytes=64) == 3
