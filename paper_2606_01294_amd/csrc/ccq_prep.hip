@@ -29,8 +29,8 @@ __device__ __forceinline__ float lane_group_sum(float x) {
 
 // A token's row is one long chain (request, norms over lane groups, gates, sums
 // over the wave), so with few tokens a wave's own time is what counts: one token
-// per wave, and the rows requested ahead of the staging of W.
-template <typename T, int DK, int HMAX, int TPW>
+// per wave, and the rows requested ahead of the staging of W (AHEAD).
+template <typename T, int DK, int HMAX, int TPW, bool AHEAD>
 __global__ __launch_bounds__(kThreads) void prep_kernel(const PrepArgs a) {
   constexpr int kPrepTokens = 4 * TPW;  // tokens per workgroup
   extern __shared__ float sW[];  // [H][H * DK], each row split in half-pieces (below)
@@ -44,20 +44,23 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const PrepArgs a) {
   const T* kr = static_cast<const T*>(a.k_raw);
   T* qo = static_cast<T*>(a.q);
   T* ko = static_cast<T*>(a.k);
-  // every piece of the wave's tokens requested first, then W_lambda
+  // every piece of the wave's tokens requested at once, ahead of W_lambda or after it
   v8 qa[TPW][NPMAX], ka[TPW][NPMAX];
+  auto request = [&] {
 #pragma unroll
-  for (int tt = 0; tt < TPW; ++tt) {
-    const long long tok = (long long)blockIdx.x * kPrepTokens + w * TPW + tt;
+    for (int tt = 0; tt < TPW; ++tt) {
+      const long long tok = (long long)blockIdx.x * kPrepTokens + w * TPW + tt;
 #pragma unroll
-    for (int i = 0; i < NPMAX; ++i) {
-      const int p = l + 64 * i;
-      if (tok < ntok && p < NP) {
-        qa[tt][i] = *reinterpret_cast<const v8*>(qr + (size_t)tok * E + 8 * p);
-        ka[tt][i] = *reinterpret_cast<const v8*>(kr + (size_t)tok * E + 8 * p);
+      for (int i = 0; i < NPMAX; ++i) {
+        const int p = l + 64 * i;
+        if (tok < ntok && p < NP) {
+          qa[tt][i] = *reinterpret_cast<const v8*>(qr + (size_t)tok * E + 8 * p);
+          ka[tt][i] = *reinterpret_cast<const v8*>(kr + (size_t)tok * E + 8 * p);
+        }
       }
     }
-  }
+  };
+  if constexpr (AHEAD) request();
   {  // W_lambda into LDS: every 16-byte piece requested before any is stored
     constexpr int NW4 = (int)(kPrepMaxLds / 16 / kThreads);
     const int n4 = H * E / 4;
@@ -80,6 +83,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const PrepArgs a) {
     }
   }
   __syncthreads();
+  if constexpr (!AHEAD) request();
   // norms of every token's head rows; normalised rows (or the row scales) out
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
@@ -186,15 +190,27 @@ hipError_t run_prep(const PrepArgs& a, hipStream_t st) {
   const long long ntok = (long long)a.B * a.T;
   if (ntok == 0 || a.H == 0) return hipSuccess;
   const size_t lds = (size_t)a.H * a.H * DK * sizeof(float);
-  // one token per wave while the workgroups of four tokens fit the chip at once
-  // (two per compute unit by the LDS of W_lambda)
-  if (ntok <= 4 * 512) {
-    hipLaunchKernelGGL((prep_kernel<T, DK, kPrepMaxHeads, 1>), dim3((unsigned)((ntok + 3) / 4)), dim3(kThreads), lds, st,
-                       a);
+  // One token per wave while the workgroups of four tokens fit the chip at once
+  // (two per compute unit by the LDS of W_lambda): us with one against four at 2048
+  // tokens 20.2 / 22.9 (8 heads of 256), 18.5 / 19.5 (11 of 128), 15.8 / 16.2 (14 of
+  // 64), at 2304 29.6 / 23.4, 27.5 / 19.7, 19.2 / 16.3.  With 16 heads, whose W_lambda
+  // is the largest beside a row, only while a compute unit stages it once: 16 of
+  // 64, 14.8 / 16.7 at 1024 tokens, 17.1 / 16.7 at 1100, 18.0 / 17.2 at 2048 (fp32
+  // 19.3 / 18.8).
+  if (ntok <= (a.H > 14 ? 4 * 256 : 4 * 512)) {
+    hipLaunchKernelGGL((prep_kernel<T, DK, kPrepMaxHeads, 1, true>), dim3((unsigned)((ntok + 3) / 4)), dim3(kThreads),
+                       lds, st, a);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((prep_kernel<T, DK, kPrepMaxHeads, 4>), dim3((unsigned)((ntok + 15) / 16)), dim3(kThreads), lds, st,
-                     a);
+  // With four, the rows ahead of W_lambda only where there is a second round of
+  // workgroups: loads return in order, so W_lambda waits for the rows (8 heads of
+  // 256: 30.1 after, 31.0 ahead at 4500 tokens, 66.6 after, 65.4 ahead at 16384; 16 of
+  // 64: 22.1 / 22.4 and 47.1 / 45.3).
+  const dim3 grid((unsigned)((ntok + 15) / 16));
+  if (ntok <= 16 * 512)
+    hipLaunchKernelGGL((prep_kernel<T, DK, kPrepMaxHeads, 4, false>), grid, dim3(kThreads), lds, st, a);
+  else
+    hipLaunchKernelGGL((prep_kernel<T, DK, kPrepMaxHeads, 4, true>), grid, dim3(kThreads), lds, st, a);
   return hipGetLastError();
 }
 template <typename T>

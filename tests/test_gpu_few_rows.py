@@ -1,6 +1,7 @@
 """Kernels that split their work differently where there is little of it: the segment prefix of
 the key statistics (segments over the waves of a workgroup with few heads) and the
-pre-processing pass (one token per wave up to 2048 tokens).  Parity with the oracle on both
+pre-processing pass (one token per wave up to 2048 tokens, or 1024 with the most heads, and the
+order of its loads above 8192).  Parity with the oracle on both
 sides of each rule; fp32 io is held to 1e-4 and bf16 rows to 2e-2 of the largest value, as in
 the other parity tests."""
 import numpy as np
@@ -46,8 +47,8 @@ def test_segment_prefix(lens, H, dk, cont):
         assert e <= 1e-4, (key, e)
 
 
-@pytest.mark.parametrize("T", [1, 3, 5, 2048, 2049, 2061])
-@pytest.mark.parametrize("H,dk", [(8, 256), (3, 64)])
+@pytest.mark.parametrize("T,H,dk", [(T, H, dk) for H, dk in ((8, 256), (3, 64)) for T in (1, 3, 5, 2048, 2049, 2061)] +
+                         [(1024, 16, 64), (1025, 15, 64), (8192, 2, 64), (8193, 4, 128)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_preprocessing_token_split(T, H, dk, dtype):
     print("preprocessing", T, H, dk, dtype, flush=True)
