@@ -430,7 +430,8 @@ __global__ __launch_bounds__(64 * NW, 1) void clean_out_kernel(const CleanArgs a
   // Sigma x and m . x); in the dq pass (a.back) x, the base and m . x, while the
   // output dq is the caller's
   const Seq sw = padded_rows(sq, b, a.T);
-  const Seq srx = a.back ? sw : sq, sro = a.back ? sq : sw;
+  const bool back = TRAIN && a.back;
+  const Seq srx = back ? sw : sq, sro = back ? sq : sw;
   const int cbeg = s * a.seg, cend = min(n_chunks(sq.len), cbeg + a.seg);
   if (cbeg >= cend) return;  // a segment past a packed sequence's end
   const int tid = threadIdx.x;

@@ -48,7 +48,6 @@ struct CleanArgs {
   // tensors (length cut at T), or null for a padded [B, T, H, d] batch; the
   // workspace keeps its padded per-chunk layout either way
   const int* cu = nullptr;
-  bool back = false;  // the dq pass: x, base and mdot are workspace rows, the output the caller's
   // raw q, k with per-row l2 normalisation folded in: token t, head h is scaled
   // by rq / rk [rows, H] fp32 (1 / max(|x|, eps)) as it is staged, or null
   const float* rq = nullptr;
@@ -60,6 +59,7 @@ struct CleanArgs {
   // decayed counts
   const float* la = nullptr;
   float* sdec = nullptr;  // [B*H, NS, 2] workspace: each segment's weight sum and decay
+  bool back = false;  // the dq pass: x, base and mdot are workspace rows, the output the caller's
 };
 
 // GLA state recurrence (sequential over chunks) for one 64-channel tile of S.
